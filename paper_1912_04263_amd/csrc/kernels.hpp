@@ -12,6 +12,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <type_traits>
 
@@ -49,6 +50,16 @@ struct DevState {
   int32_t pcg_sum;       // PCG iterations of the completed speculative ADMM iterations
   int32_t pcg_max;       // and their largest count
   double norms[24];   // residual-check outputs (OpUpdate<CHECK> or OpRPrim / OpRDual: 0..13, OpInfeasA/B: 16..22)
+  // in the host's copy only: the number of the host read it belongs to, written after the rest
+  uint32_t seq;
+  int32_t pad_;
+};
+
+// A host read of the device scalars: where the kernel launched last before it leaves a copy
+// (mapped host memory; null: no read follows) and the number that marks the copy as complete.
+struct HostRead {
+  DevState* to = nullptr;
+  uint32_t seq = 0;
 };
 
 struct RedBuf {
@@ -211,26 +222,34 @@ __device__ __forceinline__ void gather_partials(const double* __restrict__ parti
 
 // One 1024-thread workgroup: combine `count` partials in a fixed order (thread t takes
 // workgroups t, t + 1024, …; then a fixed tree) and run the scalar finalisation, unless the gate
-// is set; then, when `mirror` is given (only before a host read: the write crosses PCIe), copy the
-// device scalars into host-visible memory, gate or not.
+// is set; then, before a host read (the write crosses PCIe), copy the device scalars into
+// host-visible memory, gate or not.
 // Measured on checks of a 320-variable problem (8 slots): 12.6 µs with LDS permutes, one thread's
 // serial chains and a one-thread copy, 6.0 µs with the lane exchanges, one thread per slot and a
 // copy by the first wavefront's lanes; the right-hand side's three slots 4.5 → 3.2 µs.
 constexpr int kFinBlock = 1024;
 
-template <class S>
-__device__ __forceinline__ void copy_state(const S* st, S* mirror) {
-  static_assert(sizeof(S) % 8 == 0 && sizeof(S) / 8 <= 64, "one 8-byte word per lane");
-  if (threadIdx.x < sizeof(S) / 8)
-    reinterpret_cast<double*>(mirror)[threadIdx.x] = reinterpret_cast<const double*>(st)[threadIdx.x];
+// The first wavefront copies the scalars to the host, one 8-byte word per lane, and then their
+// number: the release orders the words (stores of this wavefront) before it, and the host, which
+// spins on the number, reads the words after it, without waiting for the kernel's end (a spin on the
+// stream's status took Lasso, with 2–4 reads per check, 105.2 ms instead of 101.4).
+__device__ __forceinline__ void copy_state(const DevState* st, const HostRead& hr) {
+  constexpr unsigned kWords = offsetof(DevState, seq) / 8;
+  static_assert(offsetof(DevState, seq) % 8 == 0 && kWords <= 64, "one 8-byte word per lane");
+  if (threadIdx.x >= 64) return;
+  if (threadIdx.x < kWords)
+    reinterpret_cast<double*>(hr.to)[threadIdx.x] = reinterpret_cast<const double*>(st)[threadIdx.x];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // system scope, the whole wavefront's stores
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&hr.to->seq, hr.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <int NS, unsigned MAXMASK, class Fin>
 __global__ __launch_bounds__(kFinBlock) void k_finalize(const double* __restrict__ partials, int count,
                                                         Fin fin, const int32_t* __restrict__ gate,
-                                                        const DevState* st, DevState* mirror) {
+                                                        const DevState* st, HostRead hr) {
   if (gate && *gate) {
-    if (mirror) copy_state(st, mirror);
+    if (hr.to) copy_state(st, hr);
     return;
   }
   __shared__ double lds[kMaxSlots][kFinBlock / 64];
@@ -261,16 +280,13 @@ __global__ __launch_bounds__(kFinBlock) void k_finalize(const double* __restrict
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     if (threadIdx.x == 0) fin(tot);
   }
-  if (mirror) {
+  if (hr.to) {
     __syncthreads();
-    copy_state(st, mirror);
+    copy_state(st, hr);
   }
 }
 
-template <class S>
-__global__ void k_mirror(const S* st, S* mirror) {
-  copy_state(st, mirror);
-}
+static __global__ void k_mirror(const DevState* st, HostRead hr) { copy_state(st, hr); }
 
 // After the PCG iterations launched for speculative ADMM iteration k: when the solve has not
 // finished, broke down or hit the cap, set the abort flag (which gates every later kernel of the
@@ -1113,9 +1129,9 @@ __global__ __launch_bounds__(kBlock) void k_pcg_dir(int n, T* __restrict__ p,
                                                     const T* __restrict__ dinv,
                                                     DevState* st, const double* __restrict__ partials,
                                                     int count, const int32_t* __restrict__ gate, int it,
-                                                    DevState* mirror) {
+                                                    HostRead hr) {
   if (gate && *gate) {
-    if (mirror && blockIdx.x == 0) copy_state(st, mirror);
+    if (hr.to && blockIdx.x == 0) copy_state(st, hr);
     return;
   }
   double t[2];
@@ -1132,9 +1148,9 @@ __global__ __launch_bounds__(kBlock) void k_pcg_dir(int n, T* __restrict__ p,
     if (rz_new != rz_new) st->breakdown = 1;
     st->done = (t[1] <= st->thresh || it + 1 >= st->maxit || st->breakdown || !(st->kappa > 0.0)) ? 1 : 0;
   }
-  if (mirror && blockIdx.x == 0) {
+  if (hr.to && blockIdx.x == 0) {
     __syncthreads();
-    copy_state(st, mirror);
+    copy_state(st, hr);
   }
 }
 

@@ -403,7 +403,7 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
     const bool check = (k % s.check_every == 0 || k == s.max_iter);
     if (trial) {
       if (pending) {  // read the speculation's outcome first
-        hipLaunchKernelGGL(k_mirror<DevState>, dim3(1), dim3(64), 0, stream, (const DevState*)st, st_mirror_dev);
+        hipLaunchKernelGGL(k_mirror, dim3(1), dim3(64), 0, stream, (const DevState*)st, host_read());
         sync_state();
         pending = false;
         if (st_host->abort) {
@@ -791,7 +791,7 @@ int time_kernel_impl(qpg_solver* h, int kernel, int reps, double* avg_us) {
       default:
         hipLaunchKernelGGL((k_pcg_dir<T>), dim3(h->vgrid), dim3(kBlock), 0, h->stream, h->n, V.p,
                            (const T*)V.r, (const T*)V.dinv, h->st, (const double*)h->rb.vpartials, h->vgrid,
-                           (const int32_t*)nullptr, 0, (DevState*)nullptr);
+                           (const int32_t*)nullptr, 0, HostRead{});
     }
   };
   hipEvent_t e0, e1;

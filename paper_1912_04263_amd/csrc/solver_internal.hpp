@@ -127,6 +127,7 @@ struct qpg_solver {
   DevState* st = nullptr;
   DevState* st_host = nullptr;        // mapped pinned host memory, written by finalize kernels
   DevState* st_mirror_dev = nullptr;  // its device-side address
+  uint32_t reads = 0;                 // host reads asked for so far
   RedBuf rb{};
   int32_t vgrid = 1;
 
@@ -278,23 +279,35 @@ struct qpg_solver {
   void finalize(const Op& op, int count, const int32_t* gate = nullptr, bool mirror = false) {
     hipLaunchKernelGGL((k_finalize<Op::NS, Op::MAXMASK, Op>), dim3(1), dim3(kFinBlock), 0, stream,
                        (const double*)rb.partials, count, op, gate, (const DevState*)st,
-                       mirror ? st_mirror_dev : nullptr);
+                       mirror ? host_read() : HostRead{});
   }
   template <int NS, unsigned MASK, class Fin>
   void finalize_fn(const Fin& fin, int count, const int32_t* gate = nullptr, bool mirror = false) {
     hipLaunchKernelGGL((k_finalize<NS, MASK, Fin>), dim3(1), dim3(kFinBlock), 0, stream,
                        (const double*)rb.partials, count, fin, gate, (const DevState*)st,
-                       mirror ? st_mirror_dev : nullptr);
+                       mirror ? host_read() : HostRead{});
   }
 
-  // Wait for the stream and read the device scalars: the finalize kernel launched last before a
-  // host read leaves a copy of them in mapped host memory (st_host), so no copy is queued and the
-  // host polls the stream.
+  // Wait for and read the device scalars: the kernel launched last before a host read leaves a copy
+  // of them in mapped host memory (st_host) and marks it with the read's number, which the host
+  // spins on, so no copy is queued and the end of the kernel is not waited for. The stream's
+  // status is looked at now and then, so that a failed launch or a device error ends the wait.
+  HostRead host_read() { return HostRead{st_mirror_dev, ++reads}; }
   void sync_state() {
-    hipError_t e;
-    while ((e = hipStreamQuery(stream)) == hipErrorNotReady) {
+    auto here = [&]() { return __atomic_load_n(&st_host->seq, __ATOMIC_ACQUIRE) == reads; };
+    for (;;) {
+      for (int spin = 0; spin < 4096; ++spin) {
+        if (here()) return;
+#if defined(__x86_64__)
+        __builtin_ia32_pause();
+#endif
+      }
+      const hipError_t e = hipStreamQuery(stream);
+      if (e == hipErrorNotReady) continue;
+      if (e != hipSuccess) throw HipError{e, "hipStreamQuery"};
+      if (here()) return;  // written before the stream's end was seen
+      throw HipError{hipErrorUnknown, "host read of the device scalars"};
     }
-    if (e != hipSuccess) throw HipError{e, "hipStreamQuery"};
   }
 
   template <typename T>
@@ -317,7 +330,7 @@ struct qpg_solver {
                        (track_zt && !eqrow) ? V.zt : (T*)nullptr, (const T*)V.w, (T)(1.0 / rho), it);
     hipLaunchKernelGGL((k_pcg_dir<T>), dim3(vgrid), dim3(kBlock), 0, stream, n, V.p, (const T*)V.r,
                        (const T*)V.dinv, st, (const double*)rb.vpartials, vgrid, gate, it,
-                       mirror ? st_mirror_dev : (DevState*)nullptr);
+                       mirror ? host_read() : HostRead{});
     if (spec_k >= 0) hipLaunchKernelGGL(k_after_pcg<DevState>, dim3(1), dim3(64), 0, stream, st, spec_k);
   }
 
@@ -335,7 +348,7 @@ struct qpg_solver {
       int k = std::max(0, std::min(batch, maxit - issued));
       for (int i = 0; i < k; ++i)
         pcg_iteration<T>(rho, track_zt, i == k - 1, issued + i);
-      if (k == 0) hipLaunchKernelGGL(k_mirror<DevState>, dim3(1), dim3(64), 0, stream, (const DevState*)st, st_mirror_dev);
+      if (k == 0) hipLaunchKernelGGL(k_mirror, dim3(1), dim3(64), 0, stream, (const DevState*)st, host_read());
       issued += k;
       sync_state();
       if (st_host->done || issued >= maxit) break;
