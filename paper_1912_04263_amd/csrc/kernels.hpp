@@ -50,6 +50,14 @@ struct DevState {
   int32_t pcg_sum;       // PCG iterations of the completed speculative ADMM iterations
   int32_t pcg_max;       // and their largest count
   double norms[24];   // residual-check outputs (OpUpdate<CHECK> or OpRPrim / OpRDual: 0..13, OpInfeasA/B: 16..22)
+  // where a launch of the small-problem kernel (small.hpp) left the ADMM loop: ρ̄, that of the last PCG
+  // solve and that of the g in B·g; the PCG tolerance; the best normalised residual; the iteration
+  // reached; the checks since the best and those decided on the device; ρ̄ changes; whether the
+  // iteration is a check left to the host; the iteration that B·g is for
+  struct {
+    double rho, rho_b, bg_rho, eps, best;
+    int32_t k, since, checks, updates, at_check, bg_for;
+  } run;
   // in the host's copy only: the number of the host read it belongs to, written after the rest
   uint32_t seq;
   int32_t pad_;
@@ -69,9 +77,7 @@ struct RedBuf {
 
 // NaN-propagating max (a NaN residual must not disappear inside a norm).
 __device__ __forceinline__ double nmax(double a, double b) {
-  if (a != a) return a;
-  if (b != b) return b;
-  return a > b ? a : b;
+  return (a > b || a != a) ? a : b;  // b is NaN: the comparison fails
 }
 
 template <unsigned MAXMASK>
@@ -129,6 +135,24 @@ __device__ __forceinline__ T dpp_value(T x) {
   return x;
 }
 
+// Two values' halves (or odd and even 16-lane rows) traded: a holds x's lower half, then y's; b holds x's
+// upper half, then y's.
+template <bool HALVES>
+__device__ __forceinline__ void swap2(double x, double y, double& a, double& b) {
+  uint32_t xw[2], yw[2];
+  __builtin_memcpy(xw, &x, 8);
+  __builtin_memcpy(yw, &y, 8);
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const auto r = HALVES ? __builtin_amdgcn_permlane32_swap(xw[w], yw[w], false, false)
+                          : __builtin_amdgcn_permlane16_swap(xw[w], yw[w], false, false);
+    xw[w] = r[0];
+    yw[w] = r[1];
+  }
+  __builtin_memcpy(&a, xw, 8);
+  __builtin_memcpy(&b, yw, 8);
+}
+
 // The 64 lanes' values combined by the tree of offsets 32, 16, 8, 4, 2, 1 (x ← x ∘ x[lane ^ off]),
 // result in every lane; all 64 lanes active. Rotations stand in for the exclusive-ors below 16: after
 // the steps above, a lane's value depends only on its index modulo 2·off, where i + off ≡ i ^ off.
@@ -149,18 +173,81 @@ __device__ __forceinline__ double wave_reduce(int s, double x) {
   return wave_tree(x, [s](double a, double b) { return comb<MAXMASK>(s, a, b); });
 }
 
+// The trees of NS slots at once. At each of the first steps a lane hands one half of its slots to its
+// partner and takes the partner's other half, so a step costs half of the one before (for 8 slots 10
+// combinations instead of 48); every slot is still combined by its own tree above. The result of slot s
+// is in lane s·kSlotLanes<NS>; all 64 lanes active.
+template <int NS>
+constexpr int kSlotPad = NS > 4 ? 8 : NS > 2 ? 4 : NS;  // 1, 2, 4 or 8
+template <int NS>
+constexpr int kSlotLanes = 64 / kSlotPad<NS>;
+template <unsigned MAXMASK>
+__device__ __forceinline__ double comb_either(int s, int t, bool second, double a, double b) {
+  const bool ms = (MAXMASK >> s) & 1u, mt = (MAXMASK >> t) & 1u;
+  if (ms == mt) return comb<MAXMASK>(s, a, b);
+  return (second ? mt : ms) ? nmax(a, b) : a + b;
+}
+// comb for the slot that a lane holds once P slots are spread over the wavefront
+template <unsigned MAXMASK, int P>
+__device__ __forceinline__ double comb_lane(int, int lane, double a, double b) {
+  constexpr unsigned kAll = P >= 8 ? 0xFFu : P >= 4 ? 0xFu : P >= 2 ? 0x3u : 0x1u;
+  if constexpr ((MAXMASK & kAll) == 0u) return a + b;
+  if constexpr ((MAXMASK & kAll) == kAll) return nmax(a, b);
+  return ((MAXMASK >> (lane / (64 / P))) & 1u) ? nmax(a, b) : a + b;
+}
+template <int NS, unsigned MAXMASK>
+__device__ __forceinline__ double wave_reduce_slots(const double (&v)[NS]) {
+  constexpr int P = kSlotPad<NS>;
+  double x[P];
+#pragma unroll
+  for (int s = 0; s < P; ++s) x[s] = s < NS ? v[s < NS ? s : 0] : 0.0;
+  const int lane = threadIdx.x & 63;
+  if constexpr (P == 1) return wave_reduce<MAXMASK>(0, x[0]);
+  // offset 32: lanes below keep slots 0..P/2−1, lanes above the others
+  constexpr int H = P / 2;
+#pragma unroll
+  for (int s = 0; s < H; ++s) {
+    double a, b;
+    swap2<true>(x[s], x[s + H], a, b);
+    x[s] = comb_either<MAXMASK>(s, s + H, lane & 32, a, b);
+  }
+  // offset 16, the same with the 16-lane rows
+  constexpr int Q = P / 4;
+  if constexpr (P >= 4) {
+#pragma unroll
+    for (int s = 0; s < Q; ++s) {
+      double a, b;
+      swap2<false>(x[s], x[s + Q], a, b);
+      // slots here: s, s + Q in the lower half, s + H, s + Q + H in the upper
+      x[s] = comb_lane<MAXMASK, P>(s, lane, a, b);
+    }
+  } else {
+    double a, b;
+    words2(x[0], a, b, swap_rows);
+    x[0] = comb_lane<MAXMASK, P>(0, lane, a, b);
+  }
+  // offset 8: a row's two halves
+  if constexpr (P == 8) {
+    const bool up = lane & 8;
+    const double keep = up ? x[1] : x[0], give = up ? x[0] : x[1];
+    x[0] = comb_lane<MAXMASK, P>(0, lane, keep, dpp_value<kDppRor + 8>(give));
+  } else {
+    x[0] = comb_lane<MAXMASK, P>(0, lane, x[0], dpp_value<kDppShl + 8>(x[0]));
+  }
+  // offsets 4, 2, 1 towards each group's first lane
+  x[0] = comb_lane<MAXMASK, P>(0, lane, x[0], dpp_value<kDppShl + 4>(x[0]));
+  x[0] = comb_lane<MAXMASK, P>(0, lane, x[0], dpp_value<kDppXor2>(x[0]));
+  return comb_lane<MAXMASK, P>(0, lane, x[0], dpp_value<kDppXor1>(x[0]));
+}
+
 // 256-thread reduction of NS slots; the result of slot s is valid in thread s, v[0] of it
 // (v is overwritten). Fixed order: deterministic.
 template <int NS, unsigned MAXMASK>
 __device__ __forceinline__ void block_reduce(double (&v)[NS], double* lds) {
-#pragma unroll
-  for (int s = 0; s < NS; ++s) v[s] = wave_reduce<MAXMASK>(s, v[s]);
+  const double x = wave_reduce_slots<NS, MAXMASK>(v);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   __syncthreads();
-  if (lane == 0) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s) lds[s * 4 + wid] = v[s];
-  }
+  if (lane % kSlotLanes<NS> == 0 && lane / kSlotLanes<NS> < NS) lds[lane / kSlotLanes<NS> * 4 + wid] = x;
   __syncthreads();
   const int s = threadIdx.x;
   if (s < NS)
@@ -258,11 +345,9 @@ __global__ __launch_bounds__(kFinBlock) void k_finalize(const double* __restrict
 #pragma unroll
   for (int s = 0; s < NS; ++s) acc[s] = 0.0;
   gather_partials<NS, MAXMASK, kFinBlock>(partials, count, acc);
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const double x = wave_reduce<MAXMASK>(s, acc[s]);
-    if ((threadIdx.x & 63) == 0) lds[s][threadIdx.x >> 6] = x;
-  }
+  const double x = wave_reduce_slots<NS, MAXMASK>(acc);
+  const int lane = threadIdx.x & 63;
+  if (lane % kSlotLanes<NS> == 0 && lane / kSlotLanes<NS> < NS) lds[lane / kSlotLanes<NS>][threadIdx.x >> 6] = x;
   __syncthreads();
   // thread s runs slot s's chain over the wavefronts (their values loaded before the chain)
   if (threadIdx.x < NS) {
@@ -372,8 +457,10 @@ __device__ __forceinline__ T wave_sum(T x, int width) {
 //   void side() const;                  extra elementwise work (grid-stride, in k_spmv)
 //   void operator()(const double* totals) const;  scalar finalisation (run by k_finalize)
 // ----------------------------------------------------------------------------------------------
+// The product is rounded before it is added, also where the compiler sees that `first` is constant.
 template <typename T>
 __device__ __forceinline__ void accumulate(T v, T x, bool first, T& s1, T& s2) {
+#pragma clang fp contract(off)
   const T pr = v * x;
   s1 += first ? pr : T(0);
   s2 += first ? T(0) : pr;
@@ -953,6 +1040,10 @@ struct OpRDualRhs {
 // OpRhsRec from a B·g formed with ρ̄_g before a ρ̄ update: g's second part scales with ρ̄
 // (ρ_i = c_i·ρ̄ on every row), so Āᵀ(ρ̄(z̃ − z) + y) = Āᵀy + (ρ̄/ρ̄_g)·(Āᵀg_m − Āᵀy).
 template <typename T>
+__device__ __forceinline__ T rhs_rescale(T s2, T aty, T ratio) {
+  return aty + ratio * (s2 - aty);
+}
+template <typename T>
 struct OpRhsRescaled {
   QPG_NO_SIDE
   static constexpr int NS = OpRhsRec<T>::NS;
@@ -961,8 +1052,7 @@ struct OpRhsRescaled {
   const T* aty;  // Āᵀy (n)
   T ratio;       // ρ̄ / ρ̄_g
   __device__ void epilogue(int i, T s1, T s2, double* red) const {
-    const T a = aty[i];
-    rc.epilogue(i, s1, a + ratio * (s2 - a), red);
+    rc.epilogue(i, s1, rhs_rescale(s2, aty[i], ratio), red);
   }
   __device__ void operator()(const double* t) const { rc(t); }
 };
@@ -1059,6 +1149,25 @@ __device__ __forceinline__ void reduce_partials(const double* __restrict__ parti
 // and k_pcg_dir ends the solve.
 // With zt set, z̃ = Āx̃ follows x̃: z̃ += α·Āp, with Āp = w/ρ̄ from this iteration's Ā pass, so the
 // ADMM update after PCG needs no SpMV of its own.
+// The steps of one element, shared with the small-problem kernels (small.hpp).
+template <typename T>
+__device__ __forceinline__ void pcg_update_at(int i, T a, T* xt, T* r, const T* p, const T* kp, const T* dinv,
+                                              double (&red)[2]) {
+  xt[i] += a * p[i];
+  const T ri = r[i] + a * kp[i];
+  r[i] = ri;
+  red[0] += (double)ri * (double)(ri * dinv[i]);
+  red[1] = nmax(red[1], fabs((double)ri));
+}
+template <typename T>
+__device__ __forceinline__ void pcg_track_at(int i, T a, T* zt, const T* w, T rho_inv) {
+  zt[i] += a * (w[i] * rho_inv);
+}
+template <typename T>
+__device__ __forceinline__ void pcg_dir_at(int i, T b, T* p, const T* r, const T* dinv) {
+  p[i] = -(r[i] * dinv[i]) + b * p[i];
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_pcg_update(int n, T* __restrict__ xt,
                                                        T* __restrict__ r,
@@ -1084,14 +1193,8 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update(int n, T* __restrict__ xt
   double red[2] = {0.0, 0.0};
   const int total = zt ? (n > m ? n : m) : n;
   for (int i = blockIdx.x * kBlock + threadIdx.x; i < total; i += gridDim.x * kBlock) {
-    if (i < n) {
-      xt[i] += a * p[i];
-      const T ri = r[i] + a * kp[i];
-      r[i] = ri;
-      red[0] += (double)ri * (double)(ri * dinv[i]);
-      red[1] = nmax(red[1], fabs((double)ri));
-    }
-    if (zt && i < m) zt[i] += a * (w[i] * rho_inv);
+    if (i < n) pcg_update_at(i, a, xt, r, p, kp, dinv, red);
+    if (zt && i < m) pcg_track_at(i, a, zt, w, rho_inv);
   }
   publish<2, 2u>(red, partials);
 }
@@ -1139,7 +1242,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_dir(int n, T* __restrict__ p,
   const double rz_new = t[0], beta = rz_new / st->rzp[it & 1];
   const T b = (T)beta;
   for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock)
-    p[i] = -(r[i] * dinv[i]) + b * p[i];
+    pcg_dir_at(i, b, p, r, dinv);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st->rzp[(it + 1) & 1] = rz_new;
     st->beta = beta;
@@ -1157,14 +1260,19 @@ __global__ __launch_bounds__(kBlock) void k_pcg_dir(int n, T* __restrict__ p,
 // Jacobi preconditioner (Section 6.3.1): M⁻¹_ii = 1 / (diag(P̄)_i + σ + ρ̄‖Ā_i‖²); with
 // R = diag(ρ_i), (ĀᵀRĀ)_ii = ρ̄(‖Ā_i‖² + (10³ − 1)·Σ_{equality rows k} Ā_ki²).
 template <typename T>
+__device__ __forceinline__ T jacobi_at(int i, const double* diagP, const double* colsq, double sigma, double rho,
+                                       const double* colsq_eq) {
+  const double c = colsq_eq ? colsq[i] + (kRhoEq - 1.0) * colsq_eq[i] : colsq[i];
+  return (T)(1.0 / (diagP[i] + sigma + rho * c));
+}
+
+template <typename T>
 __global__ __launch_bounds__(kBlock) void k_jacobi(int n, T* __restrict__ dinv,
                                                    const double* __restrict__ diagP,
                                                    const double* __restrict__ colsq, double sigma,
                                                    double rho, const double* __restrict__ colsq_eq) {
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-    const double c = colsq_eq ? colsq[i] + (kRhoEq - 1.0) * colsq_eq[i] : colsq[i];
-    dinv[i] = (T)(1.0 / (diagP[i] + sigma + rho * c));
-  }
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock)
+    dinv[i] = jacobi_at<T>(i, diagP, colsq, sigma, rho, colsq_eq);
 }
 
 // The unscaled iterates of a solve (Section 3.3): x = D x̄, y = E ȳ / c, z = E⁻¹ z̄, in double,
@@ -1189,22 +1297,27 @@ __global__ __launch_bounds__(kBlock) void k_unscale(int n, int m, const T* __res
 // for the n P̄ columns, ρ̄(z̃ − z) + y and ρ̄z − y for the m Āᵀ columns. Run before every OpRhsR0
 // pass: the update passes keep only plane 0 current.
 template <typename T>
+__device__ __forceinline__ void pairs_at(int i, int n, int m, T* g, const T* xt, const T* zt, const T* z,
+                                         const T* y, T rho, const uint8_t* eq) {
+  const size_t ps = (size_t)n + m;
+  if (i < n) {
+    g[i] = xt[i];
+    g[ps + i] = T(0);
+  } else {
+    const int j = i - n;
+    const T r = row_rho(eq, j, rho);
+    g[i] = r * (zt[j] - z[j]) + y[j];
+    g[ps + i] = r * z[j] - y[j];
+  }
+}
+
+template <typename T>
 __global__ __launch_bounds__(kBlock) void k_pairs(int n, int m, T* __restrict__ g,
                                                   const T* __restrict__ xt, const T* __restrict__ zt,
                                                   const T* __restrict__ z, const T* __restrict__ y, T rho,
                                                   const uint8_t* __restrict__ eq) {
-  const size_t ps = (size_t)n + m;
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n + m; i += gridDim.x * kBlock) {
-    if (i < n) {
-      g[i] = xt[i];
-      g[ps + i] = T(0);
-    } else {
-      const int j = i - n;
-      const T r = row_rho(eq, j, rho);
-      g[i] = r * (zt[j] - z[j]) + y[j];
-      g[ps + i] = r * z[j] - y[j];
-    }
-  }
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n + m; i += gridDim.x * kBlock)
+    pairs_at(i, n, m, g, xt, zt, z, y, rho, eq);
 }
 
 template <typename T>

@@ -316,6 +316,18 @@ __global__ __launch_bounds__(kBlock) void k_sell_build(const Tile* __restrict__ 
   }
 }
 
+// Absolute 16-bit columns in value order from a work list's (one wavefront per chunk; setup only).
+__global__ void k_small_cols(int32_t nchunk, const Chunk* __restrict__ chunks,
+                                    const int32_t* __restrict__ wlo, const uint16_t* __restrict__ col16,
+                                    const int32_t* __restrict__ col32, uint16_t* __restrict__ out) {
+  const int32_t ci = blockIdx.x;
+  if (ci >= nchunk) return;
+  const Chunk ch = chunks[ci];
+  const int32_t lo = wlo[ci];  // −1: the tile has no window
+  for (int32_t k = threadIdx.x; k < 64 * ch.steps; k += blockDim.x)
+    out[ch.base + k] = (uint16_t)(lo >= 0 ? lo + col16[ch.cbase + k] : col32[ch.cbase + k]);
+}
+
 // Values of B = [P | Aᵀ] in CSR (unscaled): row i is row i of the full P (p_val from p_ptr[i]),
 // then column i of A (A's CSC values from a_colptr[i]), both contiguous; one wavefront per row.
 __global__ __launch_bounds__(kBlock) void k_assemble_b(int n, const int32_t* __restrict__ b_ptr,

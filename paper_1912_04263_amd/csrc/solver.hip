@@ -197,6 +197,167 @@ void qpg_solver::alloc_prec32() {
   V.ready = true;
 }
 
+// Where a problem is one for the one-workgroup kernels of small.hpp: its vectors, slots and work
+// lists fit in LDS, and the matrices are small enough for one compute unit to stream. Per ADMM
+// iteration, one workgroup against the general path: 320 variables (control, 68 KB) 14.7 against 63 µs,
+// the random class 200×400 in FP64 (0.84 MB) 73 against 117, 700×1200 in FP32 (1.3 MB) 85 against
+// 103; 300×600 in FP64 (1.8 MB) 152 against 110, measured with the limit raised.
+constexpr int64_t kSmallBytes = 3 << 19;  // values and 16-bit columns of Ā and B
+
+template <typename T>
+void qpg_solver::plan_small() {
+  SmallPlan& sp = std::is_same<T, double>::value ? small64 : small32;
+  sp = SmallPlan();
+  if (!plan_a.s_chunks || !plan_b.s_chunks) return;
+  const int64_t bytes = (plan_a.nsrc + plan_b.nsrc) * (int64_t)(sizeof(T) + sizeof(uint16_t));
+  const int ug = grid_for(std::max(n, m));
+  if (bytes > kSmallBytes || std::max({ug, plan_a.ncomb, plan_b.ncomb}) > kSmallGroups) return;
+  int64_t off = 0;
+  auto take = [&](int64_t count, int64_t size) {
+    const int64_t at = (off + 15) / 16 * 16;
+    off = at + count * size;
+    return (int32_t)std::min<int64_t>(at, INT32_MAX);
+  };
+  SmallLds& o = sp.o;
+  // wavefront partials: the largest reduction of the passes and the vector steps' two
+  o.wp = take(4 * std::max({6 * ug, 6 * plan_a.ncomb, 8 * plan_b.ncomb}), sizeof(double));
+  o.wq = take(8 * vgrid, sizeof(double));
+  o.pw = take((int64_t)n + m, sizeof(T));
+  for (int32_t* v : {&o.xt, &o.r, &o.kp, &o.dinv}) *v = take(n, sizeof(T));
+  o.zt = take(m, sizeof(T));
+  o.slots = take(std::max<int64_t>(plan_a.nslot, 2 * plan_b.nslot), sizeof(T));
+  const DevPlan* pl[2] = {&plan_a, &plan_b};
+  for (int i = 0; i < 2; ++i) {
+    o.chunk[i] = take(pl[i]->nchunk, sizeof(SmallChunk));
+    o.item[i] = take(pl[i]->ncomb, sizeof(SmallItem));
+    o.segslot[i] = take(64 * (int64_t)pl[i]->nchunk, sizeof(uint16_t));
+    o.rowslot[i] = take((int64_t)pl[i]->nrows + 1, sizeof(uint16_t));
+  }
+  const int64_t cap = (int64_t)lds_max - 1024;  // beside the kernels' static LDS
+  if (off > cap) return;
+  sp.on = true;
+  sp.lds = (size_t)off;
+  for (int32_t* v : {&o.x, &o.g}) *v = take((int64_t)n + m, sizeof(T));
+  for (int32_t* v : {&o.bk, &o.qb}) *v = take(n, sizeof(T));
+  for (int32_t* v : {&o.z, &o.lb, &o.ub}) *v = take(m, sizeof(T));
+  o.ax = take(m, sizeof(double));
+  if (off > cap) return;
+  sp.vecs = true;
+  sp.lds = (size_t)off;
+  for (int i = 0; i < 2; ++i) {
+    o.val[i] = take(pl[i]->nsrc, sizeof(T));
+    o.col[i] = take(pl[i]->nsrc, sizeof(uint16_t));
+  }
+  if (off > cap) return;
+  sp.mats = true;
+  sp.lds = (size_t)off;
+}
+
+template <typename T>
+SmallArgs<T> qpg_solver::small_args(double rho) {
+  Prec<T>& V = P<T>();
+  SmallArgs<T> a{};
+  auto mat = [](const DevPlan& pl) {
+    SmallMat<T> M{};
+    M.chunks = pl.s_chunks;
+    M.items = pl.s_items;
+    M.segslot = pl.s_segslot;
+    M.rowslot = pl.s_rowslot;
+    M.col = pl.s_col;
+    M.val = std::is_same<T, double>::value ? (const T*)pl.val64 : (const T*)pl.val32;
+    M.nchunk = pl.nchunk;
+    M.nitem = pl.ncomb;
+    M.nslot = (int32_t)pl.nslot;
+    M.nval = (int32_t)pl.nsrc;
+    M.nrows = pl.nrows;
+    return M;
+  };
+  a.A = mat(plan_a);
+  a.B = mat(plan_b);
+  a.o = small<T>().o;
+  a.x = V.x;
+  a.y = V.y;
+  a.z = V.z;
+  a.xt = V.xt;
+  a.r = V.r;
+  a.p = V.p;
+  a.dinv = V.dinv;
+  a.bk = V.bk;
+  a.zt = V.zt;
+  a.g = V.g;
+  a.bg = V.bg;
+  a.b = V.b;
+  a.qb = V.qb;
+  a.lb = V.lb;
+  a.ub = V.ub;
+  a.ax = p64.ax;
+  a.dscale = dscale;
+  a.escale = escale;
+  a.diagP = diagP;
+  a.colsq = colsq;
+  a.st = st;
+  a.n = n;
+  a.m = m;
+  a.sigma = (T)s.sigma;
+  a.alpha = (T)s.alpha;
+  a.rho = (T)rho;
+  a.rho_inv = (T)(1.0 / rho);
+  a.gamma = a.ratio = T(1);
+  a.sigma64 = s.sigma;
+  a.rho64 = rho;
+  a.maxit = s.pcg_max_iter;
+  a.rel = s.pcg_rel_test;
+  a.vgrid = vgrid;
+  a.ugrid = grid_for(std::max(n, m));
+  return a;
+}
+
+namespace {
+
+// Raise a kernel's dynamic LDS limit (a per-device attribute) before its first launch that needs it,
+// and launch it as one workgroup.
+template <typename T, bool ML, void (*KERNEL)(SmallArgs<T>)>
+void launch_small(const SmallArgs<T>& a, size_t lds, int device, hipStream_t stream) {
+  static std::atomic<size_t> allowed[64];
+  const bool tab = device >= 0 && device < 64;
+  if (!tab || lds > allowed[device].load(std::memory_order_relaxed)) {
+    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds));
+    if (tab) {
+      size_t cur = allowed[device].load(std::memory_order_relaxed);
+      while (cur < lds && !allowed[device].compare_exchange_weak(cur, lds)) {
+      }
+    }
+  }
+  hipLaunchKernelGGL(KERNEL, dim3(1), dim3(kSmallBlock<ML>), lds, stream, a);
+}
+
+}  // namespace
+
+template <typename T>
+void qpg_solver::small_admm(const SmallArgs<T>& a) {
+  const SmallPlan& sp = small<T>();
+  if (sp.mats)
+    launch_small<T, true, k_small_admm<T, true, true>>(a, sp.lds, device, stream);
+  else if (sp.vecs)
+    launch_small<T, false, k_small_admm<T, true, false>>(a, sp.lds, device, stream);
+  else
+    launch_small<T, false, k_small_admm<T, false, false>>(a, sp.lds, device, stream);
+}
+
+template <typename T>
+void qpg_solver::small_pcg(const SmallArgs<T>& a) {
+  const SmallPlan& sp = small<T>();
+  if (sp.mats)
+    launch_small<T, true, k_small_pcg<T, true>>(a, sp.lds, device, stream);
+  else
+    launch_small<T, false, k_small_pcg<T, false>>(a, sp.lds, device, stream);
+}
+template SmallArgs<double> qpg_solver::small_args<double>(double);
+template SmallArgs<float> qpg_solver::small_args<float>(double);
+template void qpg_solver::small_pcg<double>(const SmallArgs<double>&);
+template void qpg_solver::small_pcg<float>(const SmallArgs<float>&);
+
 // Infeasibility tests of Section 3.1 on the norms of OpInfeasA / OpInfeasB, every tolerance
 // relative to the ∞-norm of the difference tested (see the oracle's reading): primal first.
 int qpg_solver::infeasibility_status() const {
@@ -360,6 +521,7 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
   // stays at rounding level, in FP32 the refresh bounds it.
   constexpr int kRhsRefresh = 50;
   double rho_b = 0.0;  // ρ̄ of the PCG solve whose x̃, r and bk are in place; 0: none
+  constexpr int kTrackedPcg = 4;
   // A check's dual-residual pass also forms B·g for the next iteration (when the window of
   // pairs fits in LDS and the check's PCG solve took at most kTrackedPcg steps): that
   // iteration's recurrence then runs as a vector pass.
@@ -393,6 +555,11 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
     }
     rho_b = rho;
   };
+  // Small problems: one launch runs the iterations up to the next check and the check's device part
+  // (small.hpp); the host takes over where a PCG solve needs it, and does trials.
+  const bool fused = use_small<T>() && s.pcg_eps_schedule == 0;
+  int new_rho = 0;    // the next such launch forms g (1), and the Jacobi diagonal (2), for a new ρ̄
+  int solved_k = -1;  // iteration whose PCG solve is done while the rest of it is not
   int k = k_start;
   int it = 0;
   while (k <= s.max_iter) {
@@ -400,8 +567,87 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
     // SCS), when chosen instead of the residual rule: ε_k = max(λ·(k + 1)^(−3/2), ε_min)
     if (!fixed_eps && s.pcg_eps_schedule == 1)
       eps_pcg = std::max(s.pcg_lambda * std::pow((double)k + 1.0, -1.5), s.pcg_eps_min);
-    const bool check = (k % s.check_every == 0 || k == s.max_iter);
-    if (trial) {
+    bool check = (k % s.check_every == 0 || k == s.max_iter);
+    bool checked = false;  // the check's update and residual norms are done
+    if (fused && !trial) {
+      SmallArgs<T> a = small_args<T>(rho);
+      a.eps = eps_pcg;
+      a.k0 = k;
+      a.k1 = std::min(s.max_iter, k + kSmallIters - 1);
+      a.refresh = kRhsRefresh;
+      a.first_rhs = kRhsDirect;
+      if (rho_b > 0.0 && k % kRhsRefresh != 0) {
+        a.gamma = (T)(rho / rho_b);
+        a.first_rhs = bg_for != k ? kRhsRec : rho == bg_rho ? kRhsRows : kRhsRescaled;
+        if (a.first_rhs == kRhsRescaled) a.ratio = (T)(rho / bg_rho);
+      }
+      a.new_rho = new_rho;
+      a.zt_every = kZtReset;
+      a.exact_after = std::is_same<T, float>::value ? kTrackedPcg : INT32_MAX;
+      a.pair = pair_fits<T>();
+      a.pair_after = kTrackedPcg;
+      a.dxy = (infeas && armed) ? V.dxy : nullptr;
+      // the learned diagonal follows ρ̄ on the host, which also prints
+      a.decide = !learned_ok && !s.verbose;
+      a.since = since_best;
+      a.stall = kInfeasAfter;
+      a.rho_every = s.rho_update_every;
+      a.fixed_eps = fixed_eps;
+      a.rho_b = rho_b;
+      a.bg_rho = bg_rho;
+      a.bg_for = bg_for;
+      a.best = best_ratio;
+      a.tighten = tighten;
+      a.c = c;
+      a.q_norm = q_norm;
+      a.qb_norm = qb_norm;
+      a.gate = s.rho_update_gate;
+      a.check_every = s.check_every;
+      a.max_iter = s.max_iter;
+      a.eps_abs = s.eps_abs;
+      a.eps_rel = s.eps_rel;
+      a.lambda = s.pcg_lambda;
+      a.eps_min = s.pcg_eps_min;
+      a.hr = host_read();
+      small_admm<T>(a);
+      sync_state();
+      const auto& run = st_host->run;
+      new_rho = 0;
+      rho = run.rho;
+      rho_b = run.rho_b;
+      eps_pcg = run.eps;
+      bg_for = run.bg_for;
+      bg_rho = run.bg_rho;
+      info.rho_updates += run.updates;
+      if (run.checks > 0) {
+        best_ratio = run.best;
+        since_best = run.since;
+        armed = false;
+        const double* nm = st_host->norms;
+        info.prim_res = nm[1];
+        info.dual_res = nm[7] / c;
+        info.obj_val = (0.5 * nm[12] + nm[13]) / c;
+      }
+      k = run.k;
+      it = st_host->iter;
+      last_pcg = std::max(1, it);
+      check = (k % s.check_every == 0 || k == s.max_iter);
+      if (st_host->abort) {
+        solved_k = k;
+        const bool cut = st_host->abort_reason == 1;
+        hipLaunchKernelGGL(k_resume<DevState>, dim3(1), dim3(64), 0, stream, st, cut ? 1 : 0);
+        if (cut) it = pcg_loop<T>(rho, s.pcg_max_iter, true, it);
+      } else if (run.at_check) {
+        checked = true;
+      } else {
+        ++k;
+        continue;
+      }
+    }
+    if (checked) {
+    } else if (solved_k == k) {
+      if (after_pcg(k, it)) return finish(k);
+    } else if (trial) {
       if (pending) {  // read the speculation's outcome first
         hipLaunchKernelGGL(k_mirror, dim3(1), dim3(64), 0, stream, (const DevState*)st, host_read());
         sync_state();
@@ -459,7 +705,7 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
       if (after_pcg(k, it)) return finish(k);
     }
     T* dxy = (check && infeas && armed) ? V.dxy : nullptr;  // δx̄, δȳ of this step (Section 3.1)
-    launch_update(check, dxy, k);
+    if (!checked) launch_update(check, dxy, k);
     if (!check) {
       ++k;
       continue;
@@ -470,9 +716,8 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
     // iterations recomputes Āx̄ by an Ā pass, and a check that would stop the solve confirms the
     // primal residual by that pass first: drift can neither fake nor delay convergence there.
     {
-      constexpr int kTrackedPcg = 4;
       const bool fp32 = std::is_same<T, float>::value;
-      bool exact = !fp32;
+      bool exact = !fp32 || (checked && it > kTrackedPcg);
       auto exact_prim = [&](bool mirror) {
         OpRPrim<T> rp{V.x, V.z, escale, st};
         finalize(rp, spmv_A<T>(rp), nullptr, mirror);
@@ -481,14 +726,15 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
       if (!exact && it > kTrackedPcg) exact_prim(false);
       OpRDual<T> rd{V.x, V.y, V.qb, dscale, n, st};
       // with many PCG steps per ADMM step the saved B pass is a small share of the work
-      if (pair_fits<T>() && k < s.max_iter && it <= kTrackedPcg) {
-        finalize(rd, spmv_B_pair<T>(OpRDualRhs<T>{rd, V.g, V.bg}), nullptr, true);
+      const bool pair = pair_fits<T>() && k < s.max_iter && it <= kTrackedPcg;
+      if (!checked) {
+        finalize(rd, pair ? spmv_B_pair<T>(OpRDualRhs<T>{rd, V.g, V.bg}) : spmv_B<T>(rd), nullptr, true);
+        sync_state();
+      }
+      if (pair) {
         bg_for = k + 1;
         bg_rho = rho;
-      } else {
-        finalize(rd, spmv_B<T>(rd), nullptr, true);
       }
-      sync_state();
       const double* nm = st_host->norms;
       double prim = nm[1], nAx = nm[3], nz = nm[5];
       const double dual = nm[7] / c, nPx = nm[9] / c, nAty = nm[11] / c;
@@ -579,9 +825,12 @@ int qpg_solver::admm(int k_start, double& rho, double& eps_pcg, int& status,
                 trial = true;
               else if (use_learned)
                 learned_dinv<T>(rho);
-              else
+              else if (!fused)
                 jacobi<T>(rho);
-              pairs<T>(rho);  // g with the new ρ̄ (the check's B·g is rescaled to it)
+              if (fused && !trial)
+                new_rho = use_learned ? 1 : 2;
+              else
+                pairs<T>(rho);  // g with the new ρ̄ (the check's B·g is rescaled to it)
             }
           }
         }
@@ -854,8 +1103,40 @@ void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t
                      (const Chunk*)pl.chunks, (int64_t)t.chunks.size(), (const int32_t*)lstart,
                      (const int32_t*)llen, dcol, nnz, pl.src, t.n_src, pl.col16, t.n_c16, pl.col32, t.n_c32);
   HIPCHK(hipGetLastError());
+  pl.nchunk = (int32_t)t.chunks.size();
   pl.nslot = t.nslot;
   pl.nrows = nrows;
+  // the same list for the one-workgroup kernels
+  std::vector<SmallChunk> s_chunks;
+  std::vector<SmallItem> s_items;
+  std::vector<uint16_t> s_segslot, s_rowslot;
+  std::vector<int32_t> wlo, inv;
+  if (t.n_src * (int64_t)(sizeof(float) + sizeof(uint16_t)) <= kSmallBytes && n <= kSmallCols - m &&
+      t.nslot < kSmallCols) {
+    s_chunks.resize(t.chunks.size());
+    wlo.resize(t.chunks.size());
+    for (const Tile& x : t.tiles)
+      for (int32_t ci = x.chunk0; ci < x.chunk0 + x.nchunk; ++ci) {
+        s_chunks[ci] = SmallChunk{t.chunks[ci].base, t.chunks[ci].steps};
+        wlo[ci] = x.wlen > 0 ? x.wlo : -1;
+      }
+    for (const CombItem& c : t.comb) s_items.push_back({(uint16_t)c.r0, (uint16_t)c.r1, std::max(c.lg, 0)});
+    inv.assign((size_t)t.nslot, 0);
+    for (size_t q = 0; q < t.slotidx.size(); ++q) inv[t.slotidx[q]] = (int32_t)q;
+    s_segslot.resize(t.segslot.size());
+    for (size_t q = 0; q < t.segslot.size(); ++q)
+      s_segslot[q] = t.segslot[q] >= 0 ? (uint16_t)inv[t.segslot[q]] : (uint16_t)kSmallCols;
+    s_rowslot.assign(t.rowslot.begin(), t.rowslot.end());
+    s_rowslot.resize((size_t)nrows + 1, s_rowslot.empty() ? (uint16_t)0 : s_rowslot.back());
+    pl.s_chunks = upload(s_chunks);
+    pl.s_items = upload(s_items);
+    pl.s_segslot = upload(s_segslot);
+    pl.s_rowslot = upload(s_rowslot);
+    pl.s_col = alloc<uint16_t>((size_t)t.n_src);
+    if (pl.nchunk)
+      hipLaunchKernelGGL(k_small_cols, dim3(pl.nchunk), dim3(kBlock), 0, stream, pl.nchunk, (const Chunk*)pl.chunks,
+                         (const int32_t*)upload(wlo), (const uint16_t*)pl.col16, (const int32_t*)pl.col32, pl.s_col);
+  }
   // B's slots hold four planes (the two-vector pass of the checks), Ā's two
   pl.slots = alloc<double>((&pl == &plan_b ? 4 : 2) * (size_t)std::max<int64_t>(t.nslot, 1));
   pl.max_wlen = t.max_wlen;
@@ -1127,6 +1408,8 @@ int qpg_setup(qpg_solver** out, const qpg_csc* P_triu, const double* q, const qp
     if (settings->precision == QPG_MIXED) h->alloc_prec32();
     h->place_values(h->plan_a, h->p64.a_val, settings->precision == QPG_MIXED);
     h->place_values(h->plan_b, h->p64.b_val, settings->precision == QPG_MIXED);
+    h->plan_small<double>();
+    if (settings->precision == QPG_MIXED) h->plan_small<float>();
     mark("values into SELL order", h->stream);
     for (double* v : {h->p64.x, h->p64.xt, h->p64.r, h->p64.p, h->p64.kp, h->p64.b}) h->fill(v, h->n, 0.0);
     for (double* v : {h->p64.z, h->p64.y, h->p64.w, h->p64.zt, h->p64.ax}) h->fill(v, h->m, 0.0);

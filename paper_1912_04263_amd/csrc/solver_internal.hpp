@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "small.hpp"
 
 // Host exceptions at the C ABI, after the HipError handler of an entry point: allocation
 // failures and any other standard exception become error codes with the message kept in
@@ -95,8 +96,21 @@ struct DevPlan {
   int32_t nrows = 0;
   int32_t max_wlen = 0;  // largest staged window, in columns
   int64_t layout[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // see qpg_spmv_layout
+  // the list for the one-workgroup kernels (small.hpp), on matrices small enough for them
+  SmallChunk* s_chunks = nullptr;
+  SmallItem* s_items = nullptr;
+  uint16_t *s_segslot = nullptr, *s_rowslot = nullptr, *s_col = nullptr;
+  int32_t nchunk = 0;
   int32_t* src = nullptr;  // CSR index of every SELL position, on the device until the values are placed
   int64_t nsrc = 0;
+};
+
+// The one-workgroup kernels in one precision: whether the problem is one for them, and their LDS.
+struct SmallPlan {
+  bool on = false;
+  bool vecs = false, mats = false;  // the ADMM vectors, and the matrices too, are held in LDS
+  size_t lds = 0;
+  SmallLds o{};
 };
 
 struct LearnedState;  // learned-preconditioner data of a solver (learned.hip)
@@ -118,6 +132,7 @@ struct qpg_solver {
   Item *a_items = nullptr, *b_items = nullptr;  // row work lists of the learned SpMM
   int32_t na_items = 0, nb_items = 0;
   DevPlan plan_a, plan_b;  // SpMV work lists of Ā and B
+  SmallPlan small64, small32;
   int32_t win_cols = 8192;  // LDS gather window capacity (columns)
   int lds_max = 0;          // dynamic LDS per workgroup on the device (bytes)
   int32_t nnzA = 0, nnzB = 0;
@@ -359,10 +374,41 @@ struct qpg_solver {
     return st_host->iter;
   }
 
+  template <typename T>
+  const SmallPlan& small() const {
+    return std::is_same<T, double>::value ? small64 : small32;
+  }
+  // The small-problem kernels run where the plan has them, for R = ρ̄I (speculate 0: never).
+  template <typename T>
+  bool use_small() const {
+    return small<T>().on && s.speculate && !eqrow;
+  }
+  template <typename T>
+  void plan_small();
+  template <typename T>
+  SmallArgs<T> small_args(double rho);
+  template <typename T>
+  void small_admm(const SmallArgs<T>& a);
+  template <typename T>
+  void small_pcg(const SmallArgs<T>& a);
+
   // PCG on K x̃ = b with b already in P<T>().b and the threshold in st; starts from P<T>().xt.
   template <typename T>
   int pcg_solve(double rho, int maxit) {
     Prec<T>& V = P<T>();
+    if (use_small<T>()) {
+      SmallArgs<T> a = small_args<T>(rho);
+      a.maxit = maxit;
+      for (;;) {
+        a.hr = host_read();
+        small_pcg<T>(a);
+        sync_state();
+        if (st_host->done) break;
+        a.resume = 1;
+      }
+      last_pcg = std::max(1, st_host->iter);
+      return st_host->iter;
+    }
     spmv_A<T>(OpScaled<T>{V.xt, V.w, (T)rho, eqrow});
     OpR0<T> r0{V.xt, V.w, V.b, V.dinv, V.r, V.p, (T)s.sigma, n, maxit, st};
     finalize(r0, spmv_B<T>(r0));
