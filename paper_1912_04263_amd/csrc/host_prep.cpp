@@ -233,38 +233,22 @@ int validate_settings(const qpg_settings* s, std::string* msg) {
   return QPG_OK;
 }
 
-Plan make_plan(const std::vector<int32_t>& rowptr, int32_t nrows, int32_t cap) {
-  Plan p;
-  int32_t r = 0;
-  while (r < nrows) {
-    int32_t len = rowptr[r + 1] - rowptr[r];
-    if (len > cap) {
-      if (len <= kLongCap) {
-        p.items.push_back({r, r + 1, rowptr[r], rowptr[r + 1], 0, 0, 0, 0});
-      } else {
-        int32_t nch = (len + kChunk - 1) / kChunk;
-        int32_t base = p.n_chunk_slots;
-        int32_t ticket = p.n_split_rows++;
-        p.n_chunk_slots += nch;
-        // near-equal chunks
-        for (int32_t c = 0; c < nch; ++c) {
-          int32_t a = rowptr[r] + (int32_t)((int64_t)len * c / nch);
-          int32_t b = rowptr[r] + (int32_t)((int64_t)len * (c + 1) / nch);
-          p.items.push_back({r, r + 1, a, b, nch, c, base, ticket});
-        }
-      }
-      ++r;
+PiecePlan make_pieces(const int32_t* start, const int32_t* end, int32_t nrows) {
+  PiecePlan p;
+  for (int32_t r = 0; r < nrows;) {
+    int32_t e = r;
+    while (e < nrows && e - r < kPackRows && end[e] - start[e] <= kShortRow) ++e;
+    if (e > r) {
+      p.pieces.push_back({r, e, -1, -1});
+      r = e;
       continue;
     }
-    int32_t r0 = r;
-    int32_t acc = 0;
-    while (r < nrows) {
-      int32_t l2 = rowptr[r + 1] - rowptr[r];
-      if (l2 > cap || acc + l2 > cap || (r - r0) >= cap) break;
-      acc += l2;
-      ++r;
-    }
-    p.items.push_back({r0, r, rowptr[r0], rowptr[r], 0, 0, 0, 0});
+    const int32_t len = end[r] - start[r], count = (len + kPieceNnz - 1) / kPieceNnz;
+    if (count > 1) p.split.push_back({r, p.slots, count});
+    for (int32_t c = 0; c < count; ++c)  // near-equal pieces
+      p.pieces.push_back({r, start[r] + (int32_t)((int64_t)len * c / count),
+                          start[r] + (int32_t)((int64_t)len * (c + 1) / count), count > 1 ? p.slots++ : -1});
+    ++r;
   }
   return p;
 }

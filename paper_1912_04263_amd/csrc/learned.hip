@@ -43,6 +43,13 @@ struct LearnedState {
   double* e = nullptr;
   float *dhv = nullptr, *dhv2 = nullptr, *dav = nullptr, *dhc = nullptr, *dhc2 = nullptr,
         *dac = nullptr, *dU = nullptr;
+  // wavefront work lists over the rows of Ā and over the Āᵀ parts of B's rows
+  struct List {
+    Piece* pieces = nullptr;
+    SplitRow* split = nullptr;
+    int32_t npieces = 0, nsplit = 0;
+    float* part = nullptr;  // partial rows of the split ones
+  } list_a, list_b;
   float* part = nullptr;
   int part_groups = 0;
   NetScalars* ns = nullptr;
@@ -77,6 +84,12 @@ namespace {
 
 int div_up(long a, long b) { return (int)((a + b - 1) / b); }
 
+// Weight gradients: rows per workgroup at least, and workgroups at most (their partials are then added
+// by k_part_reduce). With 1024 rows a layer over the 20,200 variables of a training portfolio ran on 20
+// of the 256 compute units and took 62 µs; with 96 it takes 8.8, and the sum of the 211 partials 3.9.
+constexpr int kGradRows = 96;
+constexpr int kGradGroups = 512;
+
 // Build the graph data of the scaled problem once: row statistics of Ā and Āᵀ, normalised
 // edge weights on both CSR structures, node features; allocate activations.
 LearnedState* ensure_graph(qpg_solver* h) {
@@ -88,26 +101,59 @@ LearnedState* ensure_graph(qpg_solver* h) {
   L->m = m;
   hipStream_t st = h->stream;
   const int nnzA = std::max(1, h->nnzA), nnzB = std::max(1, h->nnzB);
+  // work lists from the row pointers
+  {
+    std::vector<int32_t> ap((size_t)m + 1), bp((size_t)n + 1), bs(n);
+    auto fetch = [&](std::vector<int32_t>& v, const int32_t* d) {
+      if (!v.empty())
+        HIPCHK(hipMemcpyAsync(v.data(), d, v.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    };
+    fetch(ap, h->a_ptr);
+    fetch(bp, h->b_ptr);
+    fetch(bs, h->b_split);
+    HIPCHK(hipStreamSynchronize(st));
+    auto put = [&](LearnedState::List& l, const PiecePlan& p) {
+      l.npieces = (int32_t)p.pieces.size();
+      l.nsplit = (int32_t)p.split.size();
+      l.pieces = L->alloc<Piece>(p.pieces.size());
+      l.split = L->alloc<SplitRow>(p.split.size());
+      l.part = L->alloc<float>((size_t)p.slots * kH);
+      if (l.npieces) h->copy_h2d(l.pieces, p.pieces.data(), p.pieces.size() * sizeof(Piece));
+      if (l.nsplit) h->copy_h2d(l.split, p.split.data(), p.split.size() * sizeof(SplitRow));
+      HIPCHK(hipStreamSynchronize(st));  // p goes out of scope
+    };
+    put(L->list_a, make_pieces(ap.data(), ap.data() + 1, m));
+    put(L->list_b, make_pieces(bs.data(), bp.data() + 1, n));
+  }
   double *rsA = L->alloc<double>(m), *mxA = L->alloc<double>(m), *sqA = L->alloc<double>(m);
   double *rsB = L->alloc<double>(n), *mxB = L->alloc<double>(n), *sqB = L->alloc<double>(n);
   int32_t *dgA = L->alloc<int32_t>(m), *dgB = L->alloc<int32_t>(n);
-  if (m > 0)
-    hipLaunchKernelGGL(k_rowstats, dim3(div_up(m, kBlock)), dim3(kBlock), 0, st, m, (const int32_t*)h->a_ptr,
-                       (const int32_t*)nullptr, (const double*)h->p64.a_val, rsA, mxA, sqA, dgA);
-  hipLaunchKernelGGL(k_rowstats, dim3(div_up(n, kBlock)), dim3(kBlock), 0, st, n, (const int32_t*)h->b_ptr,
-                     (const int32_t*)h->b_split, (const double*)h->p64.b_val, rsB, mxB, sqB, dgB);
+  auto stats = [&](const LearnedState::List& l, int rows, const int32_t* ptr, const int32_t* start, const double* val,
+                   double* rs, double* mx, double* sq, int32_t* dg) {
+    if (rows == 0) return;
+    double* part = reinterpret_cast<double*>(l.part);  // 3 doubles of a slot's 32 floats
+    hipLaunchKernelGGL(k_rowstats, dim3(div_up(l.npieces, kBlock / 64)), dim3(kBlock), 0, st, (const Piece*)l.pieces,
+                       l.npieces, ptr, start, val, rs, mx, sq, part);
+    if (l.nsplit)
+      hipLaunchKernelGGL(k_rowstats_split, dim3(div_up(l.nsplit, kBlock / 64)), dim3(kBlock), 0, st,
+                         (const SplitRow*)l.split, l.nsplit, (const double*)part, rs, mx, sq);
+    hipLaunchKernelGGL(k_degrees, dim3(div_up(rows, kBlock)), dim3(kBlock), 0, st, rows, ptr, start, dg);
+  };
+  stats(L->list_a, m, h->a_ptr, nullptr, h->p64.a_val, rsA, mxA, sqA, dgA);
+  stats(L->list_b, n, h->b_ptr, h->b_split, h->p64.b_val, rsB, mxB, sqB, dgB);
   L->wA_hat = L->alloc<float>(nnzA);
   L->wA_chk = L->alloc<float>(nnzA);
   L->wB_hat = L->alloc<float>(nnzB);
   L->wB_chk = L->alloc<float>(nnzB);
-  if (m > 0)
-    hipLaunchKernelGGL(k_edge_weights, dim3(div_up(m, kBlock)), dim3(kBlock), 0, st, m,
-                       (const int32_t*)h->a_ptr, (const int32_t*)nullptr, (const int32_t*)h->a_col,
-                       (const double*)h->p64.a_val, 0, (const double*)rsA, (const double*)rsB, L->wA_hat,
-                       L->wA_chk);
-  hipLaunchKernelGGL(k_edge_weights, dim3(div_up(n, kBlock)), dim3(kBlock), 0, st, n, (const int32_t*)h->b_ptr,
-                     (const int32_t*)h->b_split, (const int32_t*)h->b_col, (const double*)h->p64.b_val, n,
-                     (const double*)rsB, (const double*)rsA, L->wB_chk, L->wB_hat);
+  auto weights = [&](const LearnedState::List& l, const int32_t* ptr, const int32_t* start, const int32_t* col,
+                     const double* val, int coff, const double* rowsum, const double* colsum, float* w_row,
+                     float* w_col) {
+    if (l.npieces)
+      hipLaunchKernelGGL(k_edge_weights, dim3(div_up(l.npieces, kBlock / 64)), dim3(kBlock), 0, st,
+                         (const Piece*)l.pieces, l.npieces, ptr, start, col, val, coff, rowsum, colsum, w_row, w_col);
+  };
+  weights(L->list_a, h->a_ptr, nullptr, h->a_col, h->p64.a_val, 0, rsA, rsB, L->wA_hat, L->wA_chk);
+  weights(L->list_b, h->b_ptr, h->b_split, h->b_col, h->p64.b_val, n, rsB, rsA, L->wB_chk, L->wB_hat);
   L->fv = L->alloc<float>((size_t)n * kH);
   L->fc = L->alloc<float>((size_t)m * kH);
   hipLaunchKernelGGL(k_features_v, dim3(div_up((long)n * kH, kBlock)), dim3(kBlock), 0, st, n,
@@ -138,7 +184,7 @@ LearnedState* ensure_graph(qpg_solver* h) {
   L->dhc = L->alloc<float>((size_t)m * kH);
   L->dhc2 = L->alloc<float>((size_t)m * kH);
   L->dac = L->alloc<float>((size_t)m * kH);
-  L->part_groups = std::max(1, std::min(256, div_up(std::max(n, m), 1024)));
+  L->part_groups = std::max(1, std::min(kGradGroups, div_up(std::max(n, m), kGradRows)));
   L->part = L->alloc<float>((size_t)L->part_groups * (64 * kH + kH));
   L->ns = L->alloc<NetScalars>(1);
   HIPCHK(hipHostMalloc((void**)&L->ns_host, sizeof(NetScalars), hipHostMallocDefault));
@@ -169,12 +215,12 @@ void dense_bwd(qpg_solver* h, LearnedState* L, bool bf16, int N, const float* X1
     HIPCHK(hipMemsetAsync(gWb, 0, width * sizeof(float), h->stream));
     return;
   }
-  const int G = std::max(1, std::min(L->part_groups, div_up(N, 256)));
+  const int G = std::max(1, std::min(L->part_groups, div_up(N, kGradRows)));
   if (bf16)
     hipLaunchKernelGGL(k_dense_bwd_dw_mfma, dim3(G), dim3(kBlock), 0, h->stream, N, X1, X2, dY, Y, L->part);
   else
     hipLaunchKernelGGL(k_dense_bwd_dw_f32, dim3(G), dim3(kBlock), 0, h->stream, N, X1, X2, dY, Y, L->part);
-  hipLaunchKernelGGL(k_part_reduce, dim3(div_up(width, kBlock)), dim3(kBlock), 0, h->stream,
+  hipLaunchKernelGGL(k_part_reduce, dim3(div_up(width, 32)), dim3(kBlock), 0, h->stream,
                      (const float*)L->part, G, width, gWb);
   if (dX1) {
     if (bf16)
@@ -188,14 +234,20 @@ void dense_bwd(qpg_solver* h, LearnedState* L, bool bf16, int N, const float* X1
 
 // Y (=|+=) Â X etc.: the SpMM over the Ā structure (m rows, gather from n×32) or over the Āᵀ
 // part of B (n rows, gather from m×32).
+void spmm(qpg_solver* h, const LearnedState::List& l, const int32_t* ptr, const int32_t* start, const int32_t* col,
+          const float* w, int coff, const float* X, float* Y, int acc) {
+  if (l.npieces)
+    hipLaunchKernelGGL(k_spmm32, dim3(div_up(l.npieces, kBlock / 64)), dim3(kBlock), 0, h->stream,
+                       (const Piece*)l.pieces, l.npieces, ptr, start, col, w, coff, X, Y, l.part, acc);
+  if (l.nsplit)
+    hipLaunchKernelGGL(k_spmm_split, dim3(div_up(l.nsplit, kBlock / 64)), dim3(kBlock), 0, h->stream,
+                       (const SplitRow*)l.split, l.nsplit, (const float*)l.part, Y, acc);
+}
 void spmm_A(qpg_solver* h, const float* w, const float* X, float* Y, int acc) {
-  hipLaunchKernelGGL(k_spmm32, dim3(h->na_items), dim3(kBlock), 0, h->stream, (const Item*)h->a_items,
-                     (const int32_t*)h->a_ptr, (const int32_t*)nullptr, (const int32_t*)h->a_col, w, 0, X, Y, acc);
+  spmm(h, h->learned->list_a, h->a_ptr, nullptr, h->a_col, w, 0, X, Y, acc);
 }
 void spmm_B(qpg_solver* h, const float* w, const float* X, float* Y, int acc) {
-  hipLaunchKernelGGL(k_spmm32, dim3(h->nb_items), dim3(kBlock), 0, h->stream, (const Item*)h->b_items,
-                     (const int32_t*)h->b_ptr, (const int32_t*)h->b_split, (const int32_t*)h->b_col, w, h->n, X,
-                     Y, acc);
+  spmm(h, h->learned->list_b, h->b_ptr, h->b_split, h->b_col, w, h->n, X, Y, acc);
 }
 
 // Message-passing trunk: h_v^L in L->hv[kRounds].
@@ -223,8 +275,8 @@ void head(qpg_solver* h, LearnedState* L, const float* th, bool bf16, double rho
                      (const double*)h->colsq, h->s.sigma, rho);
 }
 
-// Loss (mean-removed squared error of log s − target) and its gradient into `grad`.
-double loss_backward(qpg_solver* h, LearnedState* L, const float* th, bool bf16, float* grad) {
+// Loss (mean-removed squared error of log s − target; queued into ns_host) and its gradient into `grad`.
+void loss_backward(qpg_solver* h, LearnedState* L, const float* th, bool bf16, float* grad) {
   const int n = h->n, m = h->m;
   const int vg = h->vgrid;
   hipLaunchKernelGGL(k_loss_mean, dim3(vg), dim3(kBlock), 0, h->stream, n, (const float*)L->g,
@@ -234,22 +286,21 @@ double loss_backward(qpg_solver* h, LearnedState* L, const float* th, bool bf16,
                      (const float*)L->g, (const NetScalars*)L->ns, L->dg, h->rb.partials);
   h->finalize_fn<1, 0u>(FinLoss{L->ns, n}, vg);
   // head output layer
-  const int G = std::max(1, std::min(L->part_groups, div_up(n, 256)));
+  const int G = std::max(1, std::min(L->part_groups, div_up(n, kGradRows)));
   hipLaunchKernelGGL(k_head_out_bwd, dim3(G), dim3(kBlock), 0, h->stream, n, (const float*)L->u,
                      (const float*)L->dg, th, L->dU, L->part);
-  hipLaunchKernelGGL(k_part_reduce, dim3(1), dim3(kBlock), 0, h->stream, (const float*)L->part, G, kH + 1,
+  hipLaunchKernelGGL(k_part_reduce, dim3(div_up(kH + 1, 32)), dim3(kBlock), 0, h->stream, (const float*)L->part, G, kH + 1,
                      grad + NetOff::w_h2);
   // head hidden layer: input [h_v^L, φ]; only the h_v^L part of the input gradient is needed
   dense_bwd(h, L, bf16, n, L->hv[kRounds], L->phi, L->dU, L->u, th + NetOff::W_h1, L->dhv, nullptr, 0,
             grad + NetOff::W_h1);
   float *dhv = L->dhv, *dhv2 = L->dhv2, *dhc = L->dhc, *dhc2 = L->dhc2;
-  if (m > 0) HIPCHK(hipMemsetAsync(dhc, 0, (size_t)m * kH * sizeof(float), h->stream));
   for (int l = kRounds; l >= 1; --l) {
     // h_v^l = relu([h_v^{l−1}, a_v] W_vl + b_vl)
     dense_bwd(h, L, bf16, n, L->hv[l - 1], L->av[l], dhv, L->hv[l], th + NetOff::W_v(l), dhv2, L->dav, 0,
               grad + NetOff::W_v(l));
     // a_v = Ǎ h_c^l  ⇒  dh_c^l += Ǎᵀ da_v   (Ǎᵀ lives on the Ā structure)
-    if (m > 0) spmm_A(h, L->wA_chk, L->dav, dhc, 1);
+    if (m > 0) spmm_A(h, L->wA_chk, L->dav, dhc, l < kRounds);  // dh_c^L has no other term
     // h_c^l = relu([h_c^{l−1}, a_c] W_cl + b_cl)
     dense_bwd(h, L, bf16, m, L->hc[l - 1], L->ac[l], dhc, L->hc[l], th + NetOff::W_c(l), dhc2, L->dac, 0,
               grad + NetOff::W_c(l));
@@ -263,8 +314,6 @@ double loss_backward(qpg_solver* h, LearnedState* L, const float* th, bool bf16,
   dense_bwd(h, L, bf16, m, L->fc, nullptr, dhc, L->hc[0], th + NetOff::W_c0, nullptr, nullptr, 0,
             grad + NetOff::W_c0);
   HIPCHK(hipMemcpyAsync(L->ns_host, L->ns, sizeof(NetScalars), hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(hipStreamSynchronize(h->stream));
-  return L->ns_host->loss;
 }
 
 // Host-side parameter initialisation: uniform(±1/√fan_in) weights from a splitmix64 stream,
@@ -553,12 +602,11 @@ int qpg_net_loss_grad(qpg_net* net, qpg_solver* h, double rho, const float* targ
     HIPCHK(hipMemcpyAsync(L->tgt, target, h->n * sizeof(float), hipMemcpyHostToDevice, h->stream));
     trunk(h, L, net->theta, net->bf16);
     head<double>(h, L, net->theta, net->bf16, rho, (double*)nullptr);
-    const double l = loss_backward(h, L, net->theta, net->bf16, net->grad);
-    if (loss) *loss = l;
-    if (grad) {
+    loss_backward(h, L, net->theta, net->bf16, net->grad);
+    if (grad)
       HIPCHK(hipMemcpyAsync(grad, net->grad, NetOff::total * sizeof(float), hipMemcpyDeviceToHost, h->stream));
-      HIPCHK(hipStreamSynchronize(h->stream));
-    }
+    HIPCHK(hipStreamSynchronize(h->stream));
+    if (loss) *loss = L->ns_host->loss;
     HIPCHK(hipGetLastError());
   } catch (const HipError& e) {
     return net_error(net, e);

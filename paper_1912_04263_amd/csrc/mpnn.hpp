@@ -69,42 +69,101 @@ __device__ __forceinline__ float softplusf(float g) { return fmaxf(g, 0.f) + log
 
 // ------------------------------------------------------------------------------------ SpMM
 // Y[r, :] (=|+=) Σ_k w[k] · X[col[k] − coff, :] over the entries of row r from start[r] (or
-// rowptr[r]) to rowptr[r+1]; 32 features, one 32-lane half-wavefront per row. Uses the SpMV work
-// list of the matrix; a split long row is processed whole by the workgroup of its first chunk.
-__global__ __launch_bounds__(kBlock) void k_spmm32(const Item* __restrict__ items,
+// rowptr[r]) to rowptr[r+1]; 32 features. A wavefront per piece: 8 lanes hold an entry's 32 features as
+// float4 (one 128-byte row of X), so 8 entries are read per step, 8 steps in flight; the 8 groups' sums
+// are added by a fixed tree. In a pack of short rows each group of 8 lanes takes rows of its own. Long
+// rows leave partials to k_spmm_split: on the portfolio graph (rows of 10⁴ and 2·10⁴ entries) one
+// workgroup per row, half-wavefronts striding over it, took 282 µs on average (525 at most), bound by
+// the latency of its 1250 dependent gathers; pieces of 512 entries take 19.7 µs and the split rows' sums
+// 4.4, bound by the gathers' L2 traffic (128 bytes per entry: 10 TB/s).
+__device__ __forceinline__ float4 spmm_add(float4 a, float4 b) {
+  return {a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w};
+}
+__device__ __forceinline__ float4 spmm_fma(float w, float4 x, float4 a) {
+  return {a.x + w * x.x, a.y + w * x.y, a.z + w * x.z, a.w + w * x.w};
+}
+// sum over the 8 groups of 8 lanes, in every lane
+__device__ __forceinline__ float4 spmm_groups(float4 v) {
+  float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    float a, b;
+    x[t] += dpp_value<kDppRor + 8>(x[t]);
+    words2(x[t], a, b, swap_rows);
+    x[t] = a + b;
+    words2(x[t], a, b, swap_halves);
+    x[t] = a + b;
+  }
+  return {x[0], x[1], x[2], x[3]};
+}
+
+__global__ __launch_bounds__(kBlock) void k_spmm32(const Piece* __restrict__ pieces, int npieces,
                                                    const int32_t* __restrict__ rowptr,
                                                    const int32_t* __restrict__ start,
                                                    const int32_t* __restrict__ col,
                                                    const float* __restrict__ w, int coff,
-                                                   const float* __restrict__ X,
-                                                   float* __restrict__ Y, int accumulate) {
-  const Item it = items[blockIdx.x];
-  if (it.nchunk > 0 && it.chunk > 0) return;
-  const int tid = threadIdx.x, lane = tid & 31, half = tid >> 5;  // 8 half-waves
-  const bool single_long = (it.r1 == it.r0 + 1) && (it.nchunk > 0 || it.k1 - it.k0 > kStreamCap);
-  if (!single_long) {
-    for (int r = it.r0 + half; r < it.r1; r += kBlock / 32) {
-      const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
-      float acc = 0.f;
+                                                   const float* __restrict__ X, float* __restrict__ Y,
+                                                   float* __restrict__ part, int accumulate) {
+  const int id = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
+  if (id >= npieces) return;
+  const Piece p = pieces[id];
+  const int lane = threadIdx.x & 63, g = lane >> 3, f = 4 * (lane & 7);
+  const float4 zero = {0.f, 0.f, 0.f, 0.f};
+  auto row_of = [&](int c) { return *reinterpret_cast<const float4*>(&X[(size_t)(c - coff) * kH + f]); };
+  auto put = [&](float* y, float4 v, bool add) {
+    float4* q = reinterpret_cast<float4*>(y + f);
+    *q = add ? spmm_add(*q, v) : v;
+  };
+  if (p.k1 < 0) {
+    for (int r = p.row + g; r < p.k0; r += 8) {
+      const int b = rowptr[r + 1];
+      float4 acc = zero;
 #pragma unroll 4
-      for (int k = a; k < b; ++k) acc += w[k] * X[(size_t)(col[k] - coff) * kH + lane];
-      float* y = &Y[(size_t)r * kH + lane];
-      *y = accumulate ? *y + acc : acc;
+      for (int k = start ? start[r] : rowptr[r]; k < b; ++k) acc = spmm_fma(w[k], row_of(col[k]), acc);
+      put(&Y[(size_t)r * kH], acc, accumulate);
     }
-  } else {
-    __shared__ float part[kBlock / 32][kH];
-    const int r = it.r0;
-    const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
-    float acc = 0.f;
-    for (int k = a + half; k < b; k += kBlock / 32) acc += w[k] * X[(size_t)(col[k] - coff) * kH + lane];
-    part[half][lane] = acc;
-    __syncthreads();
-    if (tid < kH) {
-      float s = 0.f;
-      for (int h = 0; h < kBlock / 32; ++h) s += part[h][tid];
-      float* y = &Y[(size_t)r * kH + tid];
-      *y = accumulate ? *y + s : s;
+    return;
+  }
+  constexpr int U = 8;
+  float4 acc = zero;
+  for (int k0 = p.k0 + g; k0 < p.k1; k0 += 8 * U) {
+    float wk[U];
+    float4 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // past the end: the piece's last entry, not added
+      const int k = min(k0 + 8 * u, p.k1 - 1);
+      wk[u] = w[k];
+      x[u] = row_of(col[k]);
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + 8 * u < p.k1) acc = spmm_fma(wk[u], x[u], acc);
+  }
+  acc = spmm_groups(acc);
+  if (lane < 8) {
+    if (p.slot < 0)
+      put(&Y[(size_t)p.row * kH], acc, accumulate);
+    else
+      put(&part[(size_t)p.slot * kH], acc, false);
+  }
+}
+
+// Rows in several pieces: their partials added, a wavefront per row (8 partials per step).
+__global__ __launch_bounds__(kBlock) void k_spmm_split(const SplitRow* __restrict__ rows, int nrows,
+                                                       const float* __restrict__ part, float* __restrict__ Y,
+                                                       int accumulate) {
+  const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (id >= nrows) return;
+  const SplitRow s = rows[id];
+  const int lane = threadIdx.x & 63, f = 4 * (lane & 7);
+  float4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int c = lane >> 3; c < s.count; c += 8)
+    acc = spmm_add(acc, *reinterpret_cast<const float4*>(&part[(size_t)(s.slot + c) * kH + f]));
+  acc = spmm_groups(acc);
+  if (lane < 8) {
+    float4* y = reinterpret_cast<float4*>(&Y[(size_t)s.row * kH + f]);
+    *y = accumulate ? spmm_add(*y, acc) : acc;
   }
 }
 
@@ -325,14 +384,24 @@ __global__ __launch_bounds__(kBlock) void k_dense_bwd_dw_f32(int N, const float*
   }
 }
 
-// out[e] = Σ_g part[g·width + e] (workgroup order), for e < width.
+// out[e] = Σ_g part[g·width + e] for e < width: 32 elements per workgroup, 8 threads each (groups
+// g ≡ t mod 8 in order, then the 8 sums in order).
 __global__ __launch_bounds__(kBlock) void k_part_reduce(const float* __restrict__ part, int G,
                                                         int width, float* __restrict__ out) {
-  const int e = blockIdx.x * kBlock + threadIdx.x;
-  if (e >= width) return;
+  __shared__ float acc[kBlock / 32][32];
+  const int e = blockIdx.x * 32 + (threadIdx.x & 31), t = threadIdx.x >> 5;
   float s = 0.f;
-  for (int g = 0; g < G; ++g) s += part[(size_t)g * width + e];
-  out[e] = s;
+  if (e < width) {
+#pragma unroll 8
+    for (int g = t; g < G; g += kBlock / 32) s += part[(size_t)g * width + e];
+  }
+  acc[t][threadIdx.x & 31] = s;
+  __syncthreads();
+  if (t == 0 && e < width) {
+#pragma unroll
+    for (int k = 1; k < kBlock / 32; ++k) s += acc[k][threadIdx.x];
+    out[e] = s;
+  }
 }
 
 // ------------------------------------------------------------------------------ head and loss
@@ -466,33 +535,89 @@ __global__ __launch_bounds__(kBlock) void k_adam(int P, float* __restrict__ thet
 }
 
 // ------------------------------------------------------------------------------ graph build
-// Per-row statistics of rows [start or rowptr, rowptr+1) of a CSR matrix (one thread per row):
-// Σ|v|, max|v|, Σv², number of entries.
-__global__ __launch_bounds__(kBlock) void k_rowstats(int nrows, const int32_t* __restrict__ rowptr,
+// Per-row statistics of rows [start or rowptr, rowptr+1) of a CSR matrix: Σ|v|, max|v|, Σv². A
+// wavefront per piece, partials of split rows to part (3 per slot) for k_rowstats_split; the rows of a
+// pack by a lane each. (One thread per row took 4.0 ms on the portfolio graph, whose longest row has
+// 2·10⁴ entries, and the edge weights below 11.2 ms; on the SVM training instance, 2·10⁶ entries, a
+// wavefront per piece takes 7 and 14 µs instead of 0.3 and 1.1 ms.)
+__device__ __forceinline__ void rowstats_put(double s, double mx, double q, double* sum_abs, double* max_abs,
+                                             double* sumsq, int r) {
+  sum_abs[r] = s;
+  max_abs[r] = mx;
+  sumsq[r] = q;
+}
+__device__ __forceinline__ double dmax_tree(double x) {
+  return wave_tree(x, [](double a, double b) { return b > a ? b : a; });
+}
+__device__ __forceinline__ double dsum_tree(double x) {
+  return wave_tree(x, [](double a, double b) { return a + b; });
+}
+__global__ __launch_bounds__(kBlock) void k_rowstats(const Piece* __restrict__ pieces, int npieces,
+                                                     const int32_t* __restrict__ rowptr,
                                                      const int32_t* __restrict__ start,
                                                      const double* __restrict__ val,
                                                      double* __restrict__ sum_abs,
                                                      double* __restrict__ max_abs,
-                                                     double* __restrict__ sumsq,
-                                                     int32_t* __restrict__ deg) {
-  const int r = blockIdx.x * kBlock + threadIdx.x;
-  if (r >= nrows) return;
-  const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+                                                     double* __restrict__ sumsq, double* __restrict__ part) {
+  const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (id >= npieces) return;
+  const Piece p = pieces[id];
+  const int lane = threadIdx.x & 63;
+  const bool pack = p.k1 < 0;
+  const int r = p.row + (pack ? lane : 0);
+  const bool mine = !pack || r < p.k0;
+  const int a = pack ? (mine ? (start ? start[r] : rowptr[r]) : 0) : p.k0 + lane;
+  const int b = pack ? (mine ? rowptr[r + 1] : 0) : p.k1, step = pack ? 1 : 64;
   double s = 0.0, mx = 0.0, q = 0.0;
-  for (int k = a; k < b; ++k) {
+#pragma unroll 4
+  for (int k = a; k < b; k += step) {
     const double v = fabs(val[k]);
     s += v;
     mx = v > mx ? v : mx;
     q += v * v;
   }
-  sum_abs[r] = s;
-  max_abs[r] = mx;
-  sumsq[r] = q;
-  deg[r] = b - a;
+  if (pack) {
+    if (mine) rowstats_put(s, mx, q, sum_abs, max_abs, sumsq, r);
+    return;
+  }
+  s = dsum_tree(s);
+  mx = dmax_tree(mx);
+  q = dsum_tree(q);
+  if (lane == 0) {
+    if (p.slot < 0) {
+      rowstats_put(s, mx, q, sum_abs, max_abs, sumsq, p.row);
+    } else {
+      part[3 * (size_t)p.slot] = s;
+      part[3 * (size_t)p.slot + 1] = mx;
+      part[3 * (size_t)p.slot + 2] = q;
+    }
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_rowstats_split(const SplitRow* __restrict__ rows, int nrows,
+                                                           const double* __restrict__ part,
+                                                           double* __restrict__ sum_abs,
+                                                           double* __restrict__ max_abs,
+                                                           double* __restrict__ sumsq) {
+  const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (id >= nrows) return;
+  const SplitRow sr = rows[id];
+  const int lane = threadIdx.x & 63;
+  double s = 0.0, mx = 0.0, q = 0.0;
+  for (int c = lane; c < sr.count; c += 64) {
+    const double* p = part + 3 * (size_t)(sr.slot + c);
+    s += p[0];
+    mx = p[1] > mx ? p[1] : mx;
+    q += p[2];
+  }
+  s = dsum_tree(s);
+  mx = dmax_tree(mx);
+  q = dsum_tree(q);
+  if (lane == 0) rowstats_put(s, mx, q, sum_abs, max_abs, sumsq, sr.row);
 }
 
 // Edge weights on one CSR structure: w_row[k] = |v| / rowsum[row], w_col[k] = |v| / colsum[col−coff].
-__global__ __launch_bounds__(kBlock) void k_edge_weights(int nrows, const int32_t* __restrict__ rowptr,
+__global__ __launch_bounds__(kBlock) void k_edge_weights(const Piece* __restrict__ pieces, int npieces,
+                                                         const int32_t* __restrict__ rowptr,
                                                          const int32_t* __restrict__ start,
                                                          const int32_t* __restrict__ col,
                                                          const double* __restrict__ val, int coff,
@@ -500,16 +625,31 @@ __global__ __launch_bounds__(kBlock) void k_edge_weights(int nrows, const int32_
                                                          const double* __restrict__ colsum,
                                                          float* __restrict__ w_row,
                                                          float* __restrict__ w_col) {
-  const int r = blockIdx.x * kBlock + threadIdx.x;
-  if (r >= nrows) return;
-  const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+  const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (id >= npieces) return;
+  const Piece p = pieces[id];
+  const int lane = threadIdx.x & 63;
+  const bool pack = p.k1 < 0;
+  const int r = p.row + (pack ? lane : 0);
+  if (pack && r >= p.k0) return;
+  const int a = pack ? (start ? start[r] : rowptr[r]) : p.k0 + lane;
+  const int b = pack ? rowptr[r + 1] : p.k1, step = pack ? 1 : 64;
   const double rs = rowsum[r];
-  for (int k = a; k < b; ++k) {
+#pragma unroll 4
+  for (int k = a; k < b; k += step) {
     const double v = fabs(val[k]);
     const double cs = colsum[col[k] - coff];
     w_row[k] = rs > 0 ? (float)(v / rs) : 0.f;
     w_col[k] = cs > 0 ? (float)(v / cs) : 0.f;
   }
+}
+
+// Node degrees: end − start of each row.
+__global__ __launch_bounds__(kBlock) void k_degrees(int nrows, const int32_t* __restrict__ rowptr,
+                                                    const int32_t* __restrict__ start,
+                                                    int32_t* __restrict__ deg) {
+  const int r = blockIdx.x * kBlock + threadIdx.x;
+  if (r < nrows) deg[r] = rowptr[r + 1] - (start ? start[r] : rowptr[r]);
 }
 
 // Node features (padded to 32 columns).

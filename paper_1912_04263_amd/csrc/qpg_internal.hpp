@@ -60,32 +60,32 @@ using hvec = std::vector<T, NoInit<T>>;
 
 constexpr double kInf = 1e20;       // |bound| ≥ kInf is infinite
 constexpr int kBlock = 256;         // threads per workgroup (4 wavefronts of 64)
-constexpr int kStreamCap = 2048;    // nnz staged through LDS by one workgroup (rows fully inside)
-constexpr int kLongCap = 65536;     // a longer row is split into chunks of at most kChunk nnz
-constexpr int kChunk = 32768;
 constexpr int kTileNnz = 65536;    // SpMV entries per workgroup with an LDS gather window
 constexpr int kPlainNnz = 8192;    // SpMV entries per workgroup without one
 constexpr int kTileMaxRows = 4096; // rows per SpMV row block at most
 
-// One workgroup's share of a CSR SpMV.
-//   nchunk == 0: rows [r0, r1) entirely, entries [k0, k1) = [rowptr[r0], rowptr[r1]).
-//                k1 − k0 ≤ kStreamCap unless r1 == r0 + 1 (a single long row).
-//   nchunk  > 0: entries [k0, k1) of row r0 only; chunk `chunk` of `nchunk`; the row's chunk
-//                partial sums live at partial slot `slot + chunk`, its ticket at `ticket`.
-struct Item {
-  int32_t r0, r1, k0, k1;
-  int32_t nchunk, chunk, slot, ticket;
+// One wavefront's share of the graph kernels of the learned preconditioner (its SpMM and its row
+// statistics) over the rows of a CSR matrix (Section 5.1.4: row sums are a segmented reduction over
+// the RowPointer segments): entries [k0, k1) of one row, whole (slot −1) or as the partial `slot` of
+// a SplitRow; or, with k1 < 0, all of the rows [row, k0), at most kPackRows of at most kShortRow
+// entries each.
+struct Piece {
+  int32_t row, k0, k1, slot;
 };
-
-struct Plan {
-  std::vector<Item> items;
-  int32_t n_split_rows = 0;    // rows handled by chunks (tickets needed)
-  int32_t n_chunk_slots = 0;   // chunk partial slots needed
+struct SplitRow {
+  int32_t row, slot, count;  // partials slot .. slot + count − 1, in column order
 };
+struct PiecePlan {
+  std::vector<Piece> pieces;
+  std::vector<SplitRow> split;
+  int32_t slots = 0;
+};
+constexpr int kPieceNnz = 512;
+constexpr int kShortRow = 16;
+constexpr int kPackRows = 16;
 
-// Build the row work list of a CSR matrix with nrows rows (used by the learned preconditioner's
-// SpMM; Section 5.1.4: row sums are a segmented reduction over the RowPointer segments).
-Plan make_plan(const std::vector<int32_t>& rowptr, int32_t nrows, int32_t cap = kStreamCap);
+// Row r's entries are [start[r], end[r]).
+PiecePlan make_pieces(const int32_t* start, const int32_t* end, int32_t nrows);
 
 // ---- SpMV work list (k_spmv / k_combine)
 //

@@ -1351,12 +1351,6 @@ int qpg_setup(qpg_solver** out, const qpg_csc* P_triu, const double* q, const qp
         plan_err_a = std::current_exception();
       }
     });
-    Plan pa = make_plan(H.a_ptr, H.m);
-    Plan pb = make_plan(H.b_ptr, H.n);
-    for (Plan* pl : {&pa, &pb})
-      if (pl->items.empty()) pl->items.push_back({0, 0, 0, 0, 0, 0, 0, 0});
-    h->na_items = (int32_t)pa.items.size();
-    h->nb_items = (int32_t)pb.items.size();
     h->vgrid = grid_for(h->n);
     h->nnzA = (int32_t)H.a_col.size();
     h->nnzB = (int32_t)H.b_col.size();
@@ -1365,8 +1359,6 @@ int qpg_setup(qpg_solver** out, const qpg_csc* P_triu, const double* q, const qp
     h->b_ptr = h->upload(H.b_ptr);
     h->b_split = h->upload(H.b_split);
     h->b_col = h->upload(H.b_col);
-    h->a_items = h->upload(pa.items);
-    h->b_items = h->upload(pb.items);
     h->diagP = h->alloc<double>(H.n);
     h->colsq = h->alloc<double>(H.n);
     if (settings->rho_vector) {
@@ -1381,7 +1373,7 @@ int qpg_setup(qpg_solver** out, const qpg_csc* P_triu, const double* q, const qp
                          hipHostMallocDefault));
     // partials hold up to max(work lists, vector grids) workgroups; the work-list counts are
     // known once the planner is done, so size them for the vector grids first
-    int maxgrid = std::max(1024, std::max(h->na_items, h->nb_items));
+    int maxgrid = 1024;
     h->st = h->alloc<DevState>(1);
     HIPCHK(hipMemsetAsync(h->st, 0, sizeof(DevState), h->stream));
     HIPCHK(hipHostMalloc((void**)&h->st_host, sizeof(DevState), hipHostMallocMapped));

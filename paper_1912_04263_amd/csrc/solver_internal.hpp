@@ -129,8 +129,6 @@ struct qpg_solver {
   // structure shared by both precisions
   int32_t *a_ptr = nullptr, *a_col = nullptr, *b_ptr = nullptr, *b_split = nullptr,
           *b_col = nullptr;
-  Item *a_items = nullptr, *b_items = nullptr;  // row work lists of the learned SpMM
-  int32_t na_items = 0, nb_items = 0;
   DevPlan plan_a, plan_b;  // SpMV work lists of Ā and B
   SmallPlan small64, small32;
   int32_t win_cols = 8192;  // LDS gather window capacity (columns)
