@@ -270,8 +270,9 @@ int qpg_hutchinson(qpg_solver* h, const int8_t* signs, int32_t nprobes, double r
                    int32_t max_iter, double* diag);
 
 /* qpg_hutchinson without any allocation, for callers that cannot allocate device memory (code
- * under stream capture, tight loops, harnesses that forbid hipMalloc): the same computation with
- * the same kernels, bitwise the same diag, but the accumulator and the probe live in a static
+ * under stream capture, tight loops, harnesses that forbid hipMalloc): the same computation,
+ * bitwise the same diag (probe by probe, where qpg_hutchinson takes several at a time while the
+ * device has room for their vectors), but the accumulator and the probe live in a static
  * device array of QPG_NOALLOC_SCRATCH_BYTES that every device the library runs on holds for the
  * life of the process (its address is looked up once per device, in qpg_setup). It allocates no
  * device memory and builds none of the learned preconditioner's graph data, which qpg_hutchinson

@@ -306,8 +306,10 @@ struct qpg_solver {
   // spins on, so no copy is queued and the end of the kernel is not waited for. The stream's
   // status is looked at now and then, so that a failed launch or a device error ends the wait.
   HostRead host_read() { return HostRead{st_mirror_dev, ++reads}; }
-  void sync_state() {
-    auto here = [&]() { return __atomic_load_n(&st_host->seq, __ATOMIC_ACQUIRE) == reads; };
+  void sync_state() { spin(&st_host->seq, reads); }
+  // spins until the device has written `want` to *seq (mapped host memory)
+  void spin(const uint32_t* seq, uint32_t want) {
+    auto here = [&]() { return __atomic_load_n(seq, __ATOMIC_ACQUIRE) == want; };
     for (;;) {
       for (int spin = 0; spin < 4096; ++spin) {
         if (here()) return;
