@@ -85,12 +85,21 @@ __device__ __forceinline__ double comb(int s, double a, double b) {
   return ((MAXMASK >> s) & 1u) ? nmax(a, b) : a + b;
 }
 
-// Matrix-stream load. Plain loads: on gfx950 the non-temporal variant measured ~30% slower for
-// this access pattern (coalesced value/index streams interleaved with random gathers).
-template <typename T>
-__device__ __forceinline__ T ldm(const T* p) {
-  return *p;
+// Matrix-stream load: a plain one may stay in the caches for the next pass, the other kind passes them by.
+// Every pass reads all of Ā and B in turn, so once these exceed the 256 MB memory-side cache, plain loads
+// only push out what the next pass reads first. Then `keep32` of 32 workgroups (in groups of 8, one per
+// XCD) load plainly, a share of the matrices that stays in the cache while the rest streams past it from
+// HBM. Measured per PCG step (Ā + B): 980 MB FP64 280 µs with plain loads, 246 with none plain, 236
+// with 128 MB of them plain (192 MB: 248, 256 MB: 261); 653 MB FP64 196 / 173 / 168; 294 MB FP32 178 / 167
+// / 157; stream kernels of 10⁸ entries FP32 131 and 136 -> 109 and 114 µs (5.3–5.5 TB/s). Matrices within the cache lose by it: 163 MB FP64 85 µs plain, 91 streamed.
+template <bool KEEP, typename T>
+__device__ __forceinline__ T stream_load(const T* p) {
+  if constexpr (KEEP)
+    return *p;
+  else
+    return __builtin_nontemporal_load(p);
 }
+__device__ __forceinline__ bool stream_kept(int keep32) { return (int)((blockIdx.x >> 3) & 31) < keep32; }
 
 // Lane exchanges inside a wavefront by the vector ALU instead of LDS permutes (__shfl_xor is a
 // ds_bpermute round trip of ≈ 100 cycles per 32 bits): v_permlane32_swap / v_permlane16_swap trade
@@ -466,15 +475,19 @@ __device__ __forceinline__ void accumulate(T v, T x, bool first, T& s1, T& s2) {
   s2 += first ? T(0) : pr;
 }
 
-constexpr int kSpmvUnroll = 8;  // SELL steps in flight per lane
+constexpr int kSpmvUnroll = 8;  // SELL steps in flight per lane (k_spmv2)
 
-template <typename T, class Op>
-__global__ __launch_bounds__(kSpmvBlock) void k_spmv(const Tile* __restrict__ tiles,
+// STREAM: the matrices exceed the memory-side cache (see stream_load). Below that, 32 bytes of values in
+// flight per lane and at most 64 VGPRs, so that two workgroups share a compute unit: 3·10⁶ entries FP64 7.2 µs
+// where 90 VGPRs take 8.0; above it the registers pay (5·10⁷ entries FP64 101 µs, with 64 VGPRs 133).
+// Adding only the sum that a window can have: [P̄ | Āᵀ] with 5·10⁷ entries FP64 117.5 -> 108 µs.
+template <typename T, class Op, bool STREAM>
+__global__ __launch_bounds__(kSpmvBlock, STREAM ? 4 : 8) void k_spmv(const Tile* __restrict__ tiles,
                                                  const Chunk* __restrict__ chunks,
                                                  const int32_t* __restrict__ segslot,
                                                  const uint16_t* __restrict__ col16,
                                                  const int32_t* __restrict__ col32,
-                                                 const T* __restrict__ val, int nsplit, Op op,
+                                                 const T* __restrict__ val, int nsplit, int keep32, Op op,
                                                  T* __restrict__ slots, int64_t pstride, int planes,
                                                  const int32_t* __restrict__ gate) {
   if (gate && *gate) return;  // uniform across the grid: set before the launch
@@ -487,30 +500,55 @@ __global__ __launch_bounds__(kSpmvBlock) void k_spmv(const Tile* __restrict__ ti
     for (int i = threadIdx.x; i < t.wlen; i += kSpmvBlock) win[i] = op.gather(t.wlo + i);
     __syncthreads();
   }
+  // a window on one side of nsplit (every pass over Ā, most windows of B) needs one sum per lane: the
+  // other one stays 0
+  const int lim = nsplit - t.wlo;  // window offsets below lim belong to the first part
+  const int side = t.wlen == 0 ? 2 : lim >= t.wlen ? 0 : lim <= 0 ? 1 : 2;
   for (int ci = t.chunk0 + wave; ci < t.chunk0 + t.nchunk; ci += kSpmvBlock / 64) {
     const Chunk ch = chunks[ci];
     const int slot = segslot[ch.seg0 + lane];
-    const T* vp = val + ch.base + lane;
     T s1 = T(0), s2 = T(0);
-    if (t.wlen > 0) {
-      const uint16_t* cp = col16 + ch.cbase + lane;
-      const int lim = nsplit - t.wlo;  // window offsets below lim belong to the first part
-#pragma unroll kSpmvUnroll
-      for (int s = 0; s < ch.steps; ++s) {
-        const int o = cp[64 * s];
-        accumulate(vp[64 * s], win[o], o < lim, s1, s2);
-      }
-    } else {
-      const int32_t* cp = col32 + ch.cbase + lane;
-#pragma unroll kSpmvUnroll
-      for (int s = 0; s < ch.steps; ++s) {
-        const int c = cp[64 * s];
-        accumulate(vp[64 * s], op.gather(c), c < nsplit, s1, s2);
-      }
-    }
+    auto walk = [&](auto keep, auto both, auto get, const auto* cp, int split) {
+      const T* vp = val + ch.base + lane;
+      constexpr int kBatch = 32 / sizeof(T);
+      auto batch = [&](auto count) {
+        constexpr int U = decltype(count)::value;
+        T x[U], g[U];
+        int c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          c[u] = stream_load<decltype(keep)::value>(cp + 64 * u);
+          x[u] = stream_load<decltype(keep)::value>(vp + 64 * u);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) g[u] = get(c[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) accumulate(x[u], g[u], !decltype(both)::value || c[u] < split, s1, s2);
+        vp += 64 * U;
+        cp += 64 * U;
+      };
+      int left = ch.steps;
+      for (; left >= kBatch; left -= kBatch) batch(std::integral_constant<int, kBatch>{});
+      if constexpr (kBatch > 4)
+        if (left & 4) batch(std::integral_constant<int, 4>{});
+      if (left & 2) batch(std::integral_constant<int, 2>{});
+      if (left & 1) batch(std::integral_constant<int, 1>{});
+    };
+    auto go = [&](auto keep) {
+      if (t.wlen == 0)
+        walk(keep, std::true_type{}, [&](int c) { return op.gather(c); }, col32 + ch.cbase + lane, nsplit);
+      else if (side == 2)
+        walk(keep, std::true_type{}, [&](int o) { return win[o]; }, col16 + ch.cbase + lane, lim);
+      else
+        walk(keep, std::false_type{}, [&](int o) { return win[o]; }, col16 + ch.cbase + lane, lim);
+    };
+    if (!STREAM || stream_kept(keep32))
+      go(std::true_type{});
+    else
+      go(std::false_type{});
     if (slot >= 0) {
-      slots[slot] = s1;
-      if (planes > 1) slots[pstride + slot] = s2;
+      slots[slot] = side == 1 ? s2 : s1;
+      if (planes > 1) slots[pstride + slot] = side == 1 ? s1 : s2;
     }
   }
   op.side();
@@ -531,7 +569,7 @@ __global__ __launch_bounds__(kSpmvBlock) void k_spmv2(const Tile* __restrict__ t
                                                   const int32_t* __restrict__ segslot,
                                                   const uint16_t* __restrict__ col16,
                                                   const int32_t* __restrict__ col32,
-                                                  const T* __restrict__ val, int nsplit, Op op,
+                                                  const T* __restrict__ val, int nsplit, int keep32, Op op,
                                                   T* __restrict__ slots, int64_t pstride,
                                                   const int32_t* __restrict__ gate) {
   if (gate && *gate) return;
@@ -547,30 +585,28 @@ __global__ __launch_bounds__(kSpmvBlock) void k_spmv2(const Tile* __restrict__ t
   for (int ci = t.chunk0 + wave; ci < t.chunk0 + t.nchunk; ci += kSpmvBlock / 64) {
     const Chunk ch = chunks[ci];
     const int slot = segslot[ch.seg0 + lane];
-    const T* vp = val + ch.base + lane;
     T s1 = T(0), s2 = T(0), u1 = T(0), u2 = T(0);
-    if (t.wlen > 0) {
-      const uint16_t* cp = col16 + ch.cbase + lane;
-      const int lim = nsplit - t.wlo;
+    auto walk = [&](auto keep, auto get, const auto* cp, int split) {
+      const T* vp = val + ch.base + lane;
 #pragma unroll kSpmvUnroll
       for (int s = 0; s < ch.steps; ++s) {
-        const int o = cp[64 * s];
-        const Pair<T> x = win[o];
-        const T v = vp[64 * s];
-        accumulate(v, x.a, o < lim, s1, s2);
-        accumulate(v, x.b, o < lim, u1, u2);
+        const int c = stream_load<decltype(keep)::value>(cp + 64 * s);
+        const Pair<T> x = get(c);
+        const T v = stream_load<decltype(keep)::value>(vp + 64 * s);
+        accumulate(v, x.a, c < split, s1, s2);
+        accumulate(v, x.b, c < split, u1, u2);
       }
-    } else {
-      const int32_t* cp = col32 + ch.cbase + lane;
-#pragma unroll kSpmvUnroll
-      for (int s = 0; s < ch.steps; ++s) {
-        const int c = cp[64 * s];
-        const Pair<T> x = op.gather2(c);
-        const T v = vp[64 * s];
-        accumulate(v, x.a, c < nsplit, s1, s2);
-        accumulate(v, x.b, c < nsplit, u1, u2);
-      }
-    }
+    };
+    auto go = [&](auto keep) {
+      if (t.wlen > 0)
+        walk(keep, [&](int o) { return win[o]; }, col16 + ch.cbase + lane, nsplit - t.wlo);
+      else
+        walk(keep, [&](int c) { return op.gather2(c); }, col32 + ch.cbase + lane, nsplit);
+    };
+    if (stream_kept(keep32))
+      go(std::true_type{});
+    else
+      go(std::false_type{});
     if (slot >= 0) {
       slots[slot] = s1;
       slots[pstride + slot] = s2;

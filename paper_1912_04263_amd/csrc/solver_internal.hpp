@@ -219,14 +219,16 @@ struct qpg_solver {
   }
 
   // ----------------------------------------------------------------- launches
-  // SpMV launches (k_spmv, then k_combine); the returned count is the number of workgroup
-  // partials a finalize must combine. Segment sums go to the plan's slots and reduction partials
-  // to rb.partials unless other buffers of the same sizes are given.
-  template <typename T, class Op>
-  int spmv(const DevPlan& pl, int nsplit, int planes, const Op& op, const int32_t* gate,
-           bool combine = true, void* slots = nullptr, double* partials = nullptr) {
-    T* sl = static_cast<T*>(slots ? slots : pl.slots);
-    double* pa = partials ? partials : rb.partials;
+  // share (of 32) of the matrix passes' workgroups whose loads may stay in the memory-side cache
+  // (stream_load): all while values and columns of Ā and B fit there, else kStreamKeep bytes' worth
+  static constexpr int64_t kStreamAll = 256000000, kStreamKeep = 128000000;
+  template <typename T>
+  int stream_keep() const {
+    const int64_t bytes = ((int64_t)nnzA + nnzB) * (int64_t)(sizeof(T) + sizeof(uint16_t));
+    return bytes <= kStreamAll ? 32 : (int)(32 * kStreamKeep / bytes);
+  }
+  template <typename T, class Op, bool STREAM>
+  void spmv_stream(const DevPlan& pl, int nsplit, int planes, const Op& op, const int32_t* gate, T* sl, int keep) {
     const size_t shmem = (size_t)pl.max_wlen * sizeof(T);
     // The dynamic LDS limit is a per-device attribute of each instantiation: raise it once per
     // device (always, for device ordinals beyond the table).
@@ -234,7 +236,7 @@ struct qpg_solver {
     static std::atomic<size_t> lds_allowed[kDevTable];
     const bool tab = device >= 0 && device < kDevTable;
     if (!tab || shmem > lds_allowed[device].load(std::memory_order_relaxed)) {
-      HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_spmv<T, Op>),
+      HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_spmv<T, Op, STREAM>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem));
       if (tab) {
         size_t cur = lds_allowed[device].load(std::memory_order_relaxed);
@@ -243,8 +245,22 @@ struct qpg_solver {
       }
     }
     const T* val = std::is_same<T, double>::value ? (const T*)pl.val64 : (const T*)pl.val32;
-    hipLaunchKernelGGL((k_spmv<T, Op>), dim3(pl.ntiles), dim3(kSpmvBlock), shmem, stream, pl.tiles, pl.chunks,
-                       pl.segslot, pl.col16, pl.col32, val, nsplit, op, sl, pl.nslot, planes, gate);
+    hipLaunchKernelGGL((k_spmv<T, Op, STREAM>), dim3(pl.ntiles), dim3(kSpmvBlock), shmem, stream, pl.tiles, pl.chunks,
+                       pl.segslot, pl.col16, pl.col32, val, nsplit, keep, op, sl, pl.nslot, planes, gate);
+  }
+  // SpMV launches (k_spmv, then k_combine); the returned count is the number of workgroup
+  // partials a finalize must combine. Segment sums go to the plan's slots and reduction partials
+  // to rb.partials unless other buffers of the same sizes are given.
+  template <typename T, class Op>
+  int spmv(const DevPlan& pl, int nsplit, int planes, const Op& op, const int32_t* gate,
+           bool combine = true, void* slots = nullptr, double* partials = nullptr) {
+    T* sl = static_cast<T*>(slots ? slots : pl.slots);
+    double* pa = partials ? partials : rb.partials;
+    const int keep = stream_keep<T>();
+    if (keep < 32)
+      spmv_stream<T, Op, true>(pl, nsplit, planes, op, gate, sl, keep);
+    else
+      spmv_stream<T, Op, false>(pl, nsplit, planes, op, gate, sl, keep);
     if (!combine) return 0;
     hipLaunchKernelGGL((k_combine<T, Op>), dim3(pl.ncomb), dim3(kBlock), 0, stream, pl.comb, pl.rowslot,
                        pl.slotidx, pl.tbase, (const T*)sl, pl.nslot, planes, op, pa, gate);
@@ -282,7 +298,7 @@ struct qpg_solver {
     }
     const T* val = std::is_same<T, double>::value ? (const T*)pl.val64 : (const T*)pl.val32;
     hipLaunchKernelGGL((k_spmv2<T, Op>), dim3(pl.ntiles), dim3(kSpmvBlock), shmem, stream, pl.tiles, pl.chunks,
-                       pl.segslot, pl.col16, pl.col32, val, n, op, sl, pl.nslot, gate);
+                       pl.segslot, pl.col16, pl.col32, val, n, stream_keep<T>(), op, sl, pl.nslot, gate);
     hipLaunchKernelGGL((k_combine<T, Op>), dim3(pl.ncomb), dim3(kBlock), 0, stream, pl.comb, pl.rowslot,
                        pl.slotidx, pl.tbase, (const T*)sl, pl.nslot, 2, op, rb.partials, gate);
     return pl.ncomb;
