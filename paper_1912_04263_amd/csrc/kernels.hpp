@@ -91,7 +91,8 @@ __device__ __forceinline__ double comb(int s, double a, double b) {
 // XCD) load plainly, a share of the matrices that stays in the cache while the rest streams past it from
 // HBM. Measured per PCG step (Ā + B): 980 MB FP64 280 µs with plain loads, 246 with none plain, 236
 // with 128 MB of them plain (192 MB: 248, 256 MB: 261); 653 MB FP64 196 / 173 / 168; 294 MB FP32 178 / 167
-// / 157; stream kernels of 10⁸ entries FP32 131 and 136 -> 109 and 114 µs (5.3–5.5 TB/s). Matrices within the cache lose by it: 163 MB FP64 85 µs plain, 91 streamed.
+// / 157; stream kernels of 10⁸ entries FP32 131 and 136 -> 109 and 114 µs (5.3–5.5 TB/s).
+// Matrices within the cache lose by it: 163 MB FP64 85 µs plain, 91 streamed.
 template <bool KEEP, typename T>
 __device__ __forceinline__ T stream_load(const T* p) {
   if constexpr (KEEP)
@@ -632,6 +633,9 @@ struct NumVec<Op, std::void_t<decltype(Op::NV)>> {
 // lanes (deterministic). A grid item (lg < 0) gives each row one lane, which adds the row's K
 // slots tbase[t0 + j] + row in order: consecutive lanes read consecutive slots. Reduction
 // partials per workgroup for k_finalize.
+// Bound by the latency of the loads that follow one another (few rows: 20,000 in 79 workgroups): all
+// of a lane's go out in batches, and a batch's missing places repeat a load instead of leaving the rest to
+// a loop of single ones. Combines of [P̄ | Āᵀ] with 54 slots per row FP32 20.5 -> 7.8 µs, with 10 FP64 7.2 -> 5.0.
 template <typename T, class Op>
 __global__ __launch_bounds__(kBlock) void k_combine(const CombItem* __restrict__ items,
                                                     const int32_t* __restrict__ rowslot,
@@ -652,16 +656,39 @@ __global__ __launch_bounds__(kBlock) void k_combine(const CombItem* __restrict__
     if (r < c.r1) {
       T s1 = T(0), s2 = T(0), u1 = T(0), u2 = T(0);
       const int32_t* tb = tbase + c.t0;
-#pragma unroll 8
-      for (int j = 0; j < -c.lg; ++j) {
-        const int64_t q = (int64_t)tb[j] + r;
-        s1 += slots[q];
-        if (planes > 1) s2 += slots[pstride + q];
-        if constexpr (NV == 2) {
-          u1 += slots[2 * pstride + q];
-          u2 += slots[3 * pstride + q];
+      // batches of loads in flight; the last one repeats its last slot's load instead of running a loop of
+      // single ones
+      auto batch = [&](auto count, int j, int left) {
+        constexpr int U = decltype(count)::value;
+        T x1[U], x2[U], y1[U], y2[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int64_t q = (int64_t)tb[j + (u < left ? u : left - 1)] + r;
+          x1[u] = slots[q];
+          x2[u] = planes > 1 ? slots[pstride + q] : T(0);
+          if constexpr (NV == 2) {
+            y1[u] = slots[2 * pstride + q];
+            y2[u] = slots[3 * pstride + q];
+          }
         }
-      }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = u < left;
+          s1 = in ? s1 + x1[u] : s1;
+          s2 = in ? s2 + x2[u] : s2;
+          if constexpr (NV == 2) {
+            u1 = in ? u1 + y1[u] : u1;
+            u2 = in ? u2 + y2[u] : u2;
+          }
+        }
+      };
+      const int K = -c.lg;
+      int j = 0;
+      for (; K - j > 8; j += 16) batch(std::integral_constant<int, 16>{}, j, K - j);
+      if (K - j > 2)
+        batch(std::integral_constant<int, 8>{}, j, K - j);
+      else if (K > j)
+        batch(std::integral_constant<int, 2>{}, j, K - j);
       if constexpr (NV == 2)
         op.epilogue2(r, s1, s2, u1, u2, red);
       else
@@ -675,14 +702,30 @@ __global__ __launch_bounds__(kBlock) void k_combine(const CombItem* __restrict__
   for (int r = c.r0 + g; r < c.r1; r += groups) {
     T s1 = T(0), s2 = T(0), u1 = T(0), u2 = T(0);
     const int q1 = rowslot[r + 1];
-#pragma unroll 4
-    for (int q = rowslot[r] + lane; q < q1; q += L) {
-      const int sq = slotidx[q];
-      s1 += slots[sq];
-      if (planes > 1) s2 += slots[pstride + sq];
-      if constexpr (NV == 2) {
-        u1 += slots[2 * pstride + sq];
-        u2 += slots[3 * pstride + sq];
+    constexpr int U = 4;
+    for (int q0 = rowslot[r] + lane; q0 < q1; q0 += U * L) {
+      T x1[U], x2[U], y1[U], y2[U];
+      int sq[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) sq[u] = slotidx[q0 + u * L < q1 ? q0 + u * L : q0];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        x1[u] = slots[sq[u]];
+        x2[u] = planes > 1 ? slots[pstride + sq[u]] : T(0);
+        if constexpr (NV == 2) {
+          y1[u] = slots[2 * pstride + sq[u]];
+          y2[u] = slots[3 * pstride + sq[u]];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool in = q0 + u * L < q1;
+        s1 = in ? s1 + x1[u] : s1;
+        s2 = in ? s2 + x2[u] : s2;
+        if constexpr (NV == 2) {
+          u1 = in ? u1 + y1[u] : u1;
+          u2 = in ? u2 + y2[u] : u2;
+        }
       }
     }
     if (L > 1) {

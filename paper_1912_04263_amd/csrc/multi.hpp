@@ -195,11 +195,21 @@ __global__ __launch_bounds__(kBlock) void k_multi_combine(const CombItem* __rest
     if (r < c.r1) {
       MultiVec s1{}, s2{};
       const int32_t* tb = tbase + c.t0;
-#pragma unroll 4
-      for (int j = 0; j < -c.lg; ++j) {
-        const int64_t q = (int64_t)tb[j] + r;
-        add(s1, slots[q]);
-        if (planes > 1) add(s2, slots[pstride + q]);
+      constexpr int U = 4;
+      for (int j = 0; j < -c.lg; j += U) {
+        MultiVec x1[U], x2[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int64_t q = (int64_t)tb[j + u < -c.lg ? j + u : j] + r;
+          x1[u] = slots[q];
+          if (planes > 1) x2[u] = slots[pstride + q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (j + u < -c.lg) {
+            add(s1, x1[u]);
+            if (planes > 1) add(s2, x2[u]);
+          }
       }
       op.epilogue(r, s1, s2, red);
     }
