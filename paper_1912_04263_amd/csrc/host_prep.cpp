@@ -233,22 +233,39 @@ int validate_settings(const qpg_settings* s, std::string* msg) {
   return QPG_OK;
 }
 
-PiecePlan make_pieces(const int32_t* start, const int32_t* end, int32_t nrows) {
+PiecePlan make_pieces(const int32_t* start, const int32_t* end, const int32_t* full, int32_t nrows) {
   PiecePlan p;
+  std::vector<int32_t> chained;
+  auto len = [&](int32_t r) { return end[r] - start[r]; };
+  auto is_long = [&](int32_t r) { return full[r + 1] - full[r] > kChainRow; };
   for (int32_t r = 0; r < nrows;) {
-    int32_t e = r;
-    while (e < nrows && e - r < kPackRows && end[e] - start[e] <= kShortRow) ++e;
-    if (e > r) {
-      p.pieces.push_back({r, e, -1, -1});
-      r = e;
-      continue;
+    int32_t e = r, most = 0;
+    while (e < nrows && !is_long(e) && len(e) <= kShortRow) {
+      most = std::max(most, len(e));
+      if (e - r >= (most <= kTinyRow ? kPackRows : 8)) break;
+      ++e;
     }
-    const int32_t len = end[r] - start[r], count = (len + kPieceNnz - 1) / kPieceNnz;
-    if (count > 1) p.split.push_back({r, p.slots, count});
-    for (int32_t c = 0; c < count; ++c)  // near-equal pieces
-      p.pieces.push_back({r, start[r] + (int32_t)((int64_t)len * c / count),
-                          start[r] + (int32_t)((int64_t)len * (c + 1) / count), count > 1 ? p.slots++ : -1});
-    ++r;
+    if (e > r) {
+      p.pieces.push_back({r, e, -1});
+      r = e;
+    } else {
+      (is_long(r) ? chained : p.rows).push_back(r);
+      ++r;
+    }
+  }
+  auto longest_first = [&](std::vector<int32_t>& v) {  // so that none starts when the others end
+    std::stable_sort(v.begin(), v.end(), [&](int32_t a, int32_t b) { return len(a) > len(b); });
+  };
+  longest_first(p.rows);
+  longest_first(chained);
+  p.packs = (int32_t)p.pieces.size();
+  p.one_chain = (int32_t)p.rows.size();
+  p.rows.insert(p.rows.end(), chained.begin(), chained.end());
+  for (int32_t r : p.rows) {  // near-equal pieces
+    const int32_t count = (len(r) + kPieceNnz - 1) / kPieceNnz;
+    for (int32_t c = 0; c < count; ++c)
+      p.pieces.push_back({r, start[r] + (int32_t)((int64_t)len(r) * c / count),
+                          start[r] + (int32_t)((int64_t)len(r) * (c + 1) / count)});
   }
   return p;
 }

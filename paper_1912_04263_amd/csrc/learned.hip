@@ -44,12 +44,11 @@ struct LearnedState {
   double* e = nullptr;
   float *dhv = nullptr, *dhv2 = nullptr, *dav = nullptr, *dhc = nullptr, *dhc2 = nullptr,
         *dac = nullptr, *dU = nullptr;
-  // wavefront work lists over the rows of Ā and over the Āᵀ parts of B's rows
+  // work lists over the rows of Ā and over the Āᵀ parts of B's rows
   struct List {
     Piece* pieces = nullptr;
-    SplitRow* split = nullptr;
-    int32_t npieces = 0, nsplit = 0;
-    float* part = nullptr;  // partial rows of the split ones
+    int32_t* rows = nullptr;
+    int32_t npieces = 0, packs = 0, nrows = 0, one_chain = 0;
   } list_a, list_b;
   float* part = nullptr;
   int part_groups = 0;
@@ -123,16 +122,17 @@ LearnedState* ensure_graph(qpg_solver* h) {
     HIPCHK(hipStreamSynchronize(st));
     auto put = [&](LearnedState::List& l, const PiecePlan& p) {
       l.npieces = (int32_t)p.pieces.size();
-      l.nsplit = (int32_t)p.split.size();
+      l.packs = p.packs;
+      l.nrows = (int32_t)p.rows.size();
+      l.one_chain = p.one_chain;
       l.pieces = L->alloc<Piece>(p.pieces.size());
-      l.split = L->alloc<SplitRow>(p.split.size());
-      l.part = L->alloc<float>((size_t)p.slots * kH);
+      l.rows = L->alloc<int32_t>(p.rows.size());
       if (l.npieces) h->copy_h2d(l.pieces, p.pieces.data(), p.pieces.size() * sizeof(Piece));
-      if (l.nsplit) h->copy_h2d(l.split, p.split.data(), p.split.size() * sizeof(SplitRow));
+      if (l.nrows) h->copy_h2d(l.rows, p.rows.data(), p.rows.size() * sizeof(int32_t));
       HIPCHK(hipStreamSynchronize(st));  // p goes out of scope
     };
-    put(L->list_a, make_pieces(ap.data(), ap.data() + 1, m));
-    put(L->list_b, make_pieces(bs.data(), bp.data() + 1, n));
+    put(L->list_a, make_pieces(ap.data(), ap.data() + 1, ap.data(), m));
+    put(L->list_b, make_pieces(bs.data(), bp.data() + 1, bp.data(), n));
   }
   double *rsA = L->alloc<double>(m), *mxA = L->alloc<double>(m), *sqA = L->alloc<double>(m);
   double *rsB = L->alloc<double>(n), *mxB = L->alloc<double>(n), *sqB = L->alloc<double>(n);
@@ -140,12 +140,12 @@ LearnedState* ensure_graph(qpg_solver* h) {
   auto stats = [&](const LearnedState::List& l, int rows, const int32_t* ptr, const int32_t* start, const double* val,
                    double* rs, double* mx, double* sq, int32_t* dg) {
     if (rows == 0) return;
-    double* part = reinterpret_cast<double*>(l.part);  // 3 doubles of a slot's 32 floats
-    hipLaunchKernelGGL(k_rowstats, dim3(div_up(l.npieces, kBlock / 64)), dim3(kBlock), 0, st, (const Piece*)l.pieces,
-                       l.npieces, ptr, start, val, rs, mx, sq, part);
-    if (l.nsplit)
-      hipLaunchKernelGGL(k_rowstats_split, dim3(div_up(l.nsplit, kBlock / 64)), dim3(kBlock), 0, st,
-                         (const SplitRow*)l.split, l.nsplit, (const double*)part, rs, mx, sq);
+    if (l.packs)
+      hipLaunchKernelGGL(k_rowstats, dim3(div_up(l.packs, kBlock / 64)), dim3(kBlock), 0, st, (const Piece*)l.pieces,
+                         l.packs, ptr, start, val, rs, mx, sq);
+    if (l.nrows)
+      hipLaunchKernelGGL(k_rowstats_rows, dim3(l.nrows), dim3(64), 0, st, (const int32_t*)l.rows, ptr, start, val, rs,
+                         mx, sq);
     hipLaunchKernelGGL(k_degrees, dim3(div_up(rows, kBlock)), dim3(kBlock), 0, st, rows, ptr, start, dg);
   };
   stats(L->list_a, m, h->a_ptr, nullptr, h->p64.a_val, rsA, mxA, sqA, dgA);
@@ -245,12 +245,15 @@ void dense_bwd(qpg_solver* h, LearnedState* L, bool bf16, int N, const float* X1
 // part of B (n rows, gather from m×32).
 void spmm(qpg_solver* h, const LearnedState::List& l, const int32_t* ptr, const int32_t* start, const int32_t* col,
           const float* w, int coff, const float* X, float* Y, int acc) {
-  if (l.npieces)
-    hipLaunchKernelGGL(k_spmm32, dim3(div_up(l.npieces, kBlock / 64)), dim3(kBlock), 0, h->stream,
-                       (const Piece*)l.pieces, l.npieces, ptr, start, col, w, coff, X, Y, l.part, acc);
-  if (l.nsplit)
-    hipLaunchKernelGGL(k_spmm_split, dim3(div_up(l.nsplit, kBlock / 64)), dim3(kBlock), 0, h->stream,
-                       (const SplitRow*)l.split, l.nsplit, (const float*)l.part, Y, acc);
+  if (l.packs)
+    hipLaunchKernelGGL(k_spmm32, dim3(div_up(l.packs, kBlock / 64)), dim3(kBlock), 0, h->stream,
+                       (const Piece*)l.pieces, l.packs, ptr, start, col, w, coff, X, Y, acc);
+  if (l.one_chain)
+    hipLaunchKernelGGL((k_spmm_rows<1, 32>), dim3(l.one_chain), dim3(kSpmmBlock), 0, h->stream,
+                       (const int32_t*)l.rows, ptr, start, col, w, coff, X, Y, acc);
+  if (l.nrows > l.one_chain)
+    hipLaunchKernelGGL((k_spmm_rows<8, 8>), dim3((l.nrows - l.one_chain) * (kH / 8)), dim3(kSpmmBlock), 0, h->stream,
+                       (const int32_t*)l.rows + l.one_chain, ptr, start, col, w, coff, X, Y, acc);
 }
 void spmm_A(qpg_solver* h, const float* w, const float* X, float* Y, int acc) {
   spmm(h, h->learned->list_a, h->a_ptr, nullptr, h->a_col, w, 0, X, Y, acc);

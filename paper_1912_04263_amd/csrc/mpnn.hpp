@@ -69,101 +69,140 @@ __device__ __forceinline__ float softplusf(float g) { return fmaxf(g, 0.f) + log
 
 // ------------------------------------------------------------------------------------ SpMM
 // Y[r, :] (=|+=) Σ_k w[k] · X[col[k] − coff, :] over the entries of row r from start[r] (or
-// rowptr[r]) to rowptr[r+1]; 32 features. A wavefront per piece: 8 lanes hold an entry's 32 features as
-// float4 (one 128-byte row of X), so 8 entries are read per step, 8 steps in flight; the 8 groups' sums
-// are added by a fixed tree. In a pack of short rows each group of 8 lanes takes rows of its own. Long
-// rows leave partials to k_spmm_split: on the portfolio graph (rows of 10⁴ and 2·10⁴ entries) one
-// workgroup per row, half-wavefronts striding over it, took 282 µs on average (525 at most), bound by
-// the latency of its 1250 dependent gathers; pieces of 512 entries take 19.7 µs and the split rows' sums
-// 4.4, bound by the gathers' L2 traffic (128 bytes per entry: 10 TB/s).
-__device__ __forceinline__ float4 spmm_add(float4 a, float4 b) {
-  return {a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w};
-}
-__device__ __forceinline__ float4 spmm_fma(float w, float4 x, float4 a) {
-  return {a.x + w * x.x, a.y + w * x.y, a.z + w * x.z, a.w + w * x.w};
-}
-// sum over the 8 groups of 8 lanes, in every lane
-__device__ __forceinline__ float4 spmm_groups(float4 v) {
-  float x[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    float a, b;
-    x[t] += dpp_value<kDppRor + 8>(x[t]);
-    words2(x[t], a, b, swap_rows);
-    x[t] = a + b;
-    words2(x[t], a, b, swap_halves);
-    x[t] = a + b;
-  }
-  return {x[0], x[1], x[2], x[3]};
-}
+// rowptr[r]) to rowptr[r+1]; 32 features, each row's products added in its order (PiecePlan).
 
-__global__ __launch_bounds__(kBlock) void k_spmm32(const Piece* __restrict__ pieces, int npieces,
+// Packs of short rows: a wavefront per pack, 8 lanes per row with its 32 features as float4 (one 128-byte
+// row of X per entry), 8 or 4 entries in flight. Bound by the latency of the gathers that follow one another.
+template <int U>
+__device__ __forceinline__ float4 spmm_row(const int32_t* __restrict__ col, const float* __restrict__ w, int coff,
+                                           const float* __restrict__ X, int a, int b, int f) {
+  float4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = a; k0 < b; k0 += U) {
+    float wk[U];
+    float4 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // past the end: the row's last entry, not added
+      const int k = min(k0 + u, b - 1);
+      wk[u] = w[k];
+      x[u] = *reinterpret_cast<const float4*>(&X[(size_t)(col[k] - coff) * kH + f]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + u < b) {
+        acc.x += wk[u] * x[u].x;
+        acc.y += wk[u] * x[u].y;
+        acc.z += wk[u] * x[u].z;
+        acc.w += wk[u] * x[u].w;
+      }
+  }
+  return acc;
+}
+__global__ __launch_bounds__(kBlock) void k_spmm32(const Piece* __restrict__ packs, int npacks,
                                                    const int32_t* __restrict__ rowptr,
                                                    const int32_t* __restrict__ start,
                                                    const int32_t* __restrict__ col,
                                                    const float* __restrict__ w, int coff,
                                                    const float* __restrict__ X, float* __restrict__ Y,
-                                                   float* __restrict__ part, int accumulate) {
+                                                   int accumulate) {
   const int id = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
-  if (id >= npieces) return;
-  const Piece p = pieces[id];
-  const int lane = threadIdx.x & 63, g = lane >> 3, f = 4 * (lane & 7);
-  const float4 zero = {0.f, 0.f, 0.f, 0.f};
-  auto row_of = [&](int c) { return *reinterpret_cast<const float4*>(&X[(size_t)(c - coff) * kH + f]); };
-  auto put = [&](float* y, float4 v, bool add) {
-    float4* q = reinterpret_cast<float4*>(y + f);
-    *q = add ? spmm_add(*q, v) : v;
-  };
-  if (p.k1 < 0) {
-    for (int r = p.row + g; r < p.k0; r += 8) {
-      const int b = rowptr[r + 1];
-      float4 acc = zero;
-#pragma unroll 4
-      for (int k = start ? start[r] : rowptr[r]; k < b; ++k) acc = spmm_fma(w[k], row_of(col[k]), acc);
-      put(&Y[(size_t)r * kH], acc, accumulate);
-    }
-    return;
-  }
-  constexpr int U = 8;
-  float4 acc = zero;
-  for (int k0 = p.k0 + g; k0 < p.k1; k0 += 8 * U) {
-    float wk[U];
-    float4 x[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {  // past the end: the piece's last entry, not added
-      const int k = min(k0 + 8 * u, p.k1 - 1);
-      wk[u] = w[k];
-      x[u] = row_of(col[k]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (k0 + 8 * u < p.k1) acc = spmm_fma(wk[u], x[u], acc);
-  }
-  acc = spmm_groups(acc);
-  if (lane < 8) {
-    if (p.slot < 0)
-      put(&Y[(size_t)p.row * kH], acc, accumulate);
-    else
-      put(&part[(size_t)p.slot * kH], acc, false);
+  if (id >= npacks) return;
+  const Piece p = packs[id];
+  const int lane = threadIdx.x & 63, f = 4 * (lane & 7);
+  for (int r = p.row + (lane >> 3); r < p.k0; r += 8) {
+    const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+    const float4 v = b - a > 4 ? spmm_row<8>(col, w, coff, X, a, b, f) : spmm_row<4>(col, w, coff, X, a, b, f);
+    float4* y = reinterpret_cast<float4*>(&Y[(size_t)r * kH + f]);
+    const float4 o = accumulate ? *y : float4{0.f, 0.f, 0.f, 0.f};
+    *y = accumulate ? float4{o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w} : v;
   }
 }
 
-// Rows in several pieces: their partials added, a wavefront per row (8 partials per step).
-__global__ __launch_bounds__(kBlock) void k_spmm_split(const SplitRow* __restrict__ rows, int nrows,
-                                                       const float* __restrict__ part, float* __restrict__ Y,
-                                                       int accumulate) {
-  const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (id >= nrows) return;
-  const SplitRow s = rows[id];
-  const int lane = threadIdx.x & 63, f = 4 * (lane & 7);
-  float4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int c = lane >> 3; c < s.count; c += 8)
-    acc = spmm_add(acc, *reinterpret_cast<const float4*>(&part[(size_t)(s.slot + c) * kH + f]));
-  acc = spmm_groups(acc);
-  if (lane < 8) {
-    float4* y = reinterpret_cast<float4*>(&Y[(size_t)s.row * kH + f]);
-    *y = accumulate ? spmm_add(*y, acc) : acc;
+// Longer rows: a workgroup per row and F of its features. All 512 threads gather a batch of entries into
+// LDS, the next one's loads in flight meanwhile; CH·F lanes then add it, lane (g, f) the entries ≡ g mod
+// CH of feature f in order. On the portfolio graph (rows of 10⁴ and 2·10⁴ entries) one workgroup per row that
+// gathered as it added took 282 µs on average (525 at most); now 60 µs, bound by the chain of 2500 additions
+// of the longest row. Splitting such rows into pieces took 24 µs, but adds in another order.
+constexpr int kSpmmBlock = 512;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+template <int CH, int F>
+__global__ __launch_bounds__(kSpmmBlock, 8) void k_spmm_rows(const int32_t* __restrict__ rows,
+                                                          const int32_t* __restrict__ rowptr,
+                                                          const int32_t* __restrict__ start,
+                                                          const int32_t* __restrict__ col,
+                                                          const float* __restrict__ w, int coff,
+                                                          const float* __restrict__ X, float* __restrict__ Y,
+                                                          int accumulate) {
+  constexpr int E = 8192 / F;                  // entries of a batch
+  constexpr int LP = F / 4;                    // lanes per entry
+  constexpr int S = kSpmmBlock / LP;           // entries per load instruction of the workgroup
+  constexpr int U = E / S;
+  constexpr int W = (E + kSpmmBlock - 1) / kSpmmBlock;
+  __shared__ __align__(16) float xs[E * F];
+  __shared__ float ws[E];
+  const int r = rows[blockIdx.x / (kH / F)], f0 = (blockIdx.x % (kH / F)) * F;
+  const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+  const int tid = threadIdx.x, le = tid / LP, lf = 4 * (tid % LP);
+  if (a >= b) {  // (uniform in the workgroup)
+    if (tid < F && !accumulate) Y[(size_t)r * kH + f0 + tid] = 0.f;
+    return;
+  }
+  // loads past the end repeat the row's last entry; columns go a batch ahead of the gathers
+  floatx4 x[U];
+  float wk[W];
+  int c[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) c[u] = col[min(a + le + u * S, b - 1)];
+#pragma unroll
+  for (int u = 0; u < U; ++u) x[u] = *reinterpret_cast<const floatx4*>(&X[(size_t)(c[u] - coff) * kH + f0 + lf]);
+#pragma unroll
+  for (int u = 0; u < W; ++u) wk[u] = w[min(a + tid + u * kSpmmBlock, b - 1)];
+#pragma unroll
+  for (int u = 0; u < U; ++u) c[u] = col[min(a + E + le + u * S, b - 1)];
+  float acc = 0.f;
+  for (int k0 = a; k0 < b; k0 += E) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) *reinterpret_cast<floatx4*>(&xs[(le + u * S) * F + lf]) = x[u];
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+      if (tid + u * kSpmmBlock < E) ws[tid + u * kSpmmBlock] = wk[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = *reinterpret_cast<const floatx4*>(&X[(size_t)(c[u] - coff) * kH + f0 + lf]);
+#pragma unroll
+    for (int u = 0; u < W; ++u) wk[u] = w[min(k0 + E + tid + u * kSpmmBlock, b - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = col[min(k0 + 2 * E + le + u * S, b - 1)];
+    if (tid < CH * F) {
+      const int count = min(E, b - k0), g = tid / F, steps = (count - g + CH - 1) / CH;
+      auto add = [&](auto many, int u0) {
+        constexpr int M = decltype(many)::value;
+        float wv[M], xv[M];
+#pragma unroll
+        for (int u = 0; u < M; ++u) {
+          wv[u] = ws[(u0 + u) * CH + g];
+          xv[u] = xs[(u0 + u) * CH * F + tid];
+        }
+#pragma unroll
+        for (int u = 0; u < M; ++u) acc += wv[u] * xv[u];
+      };
+      int u = 0;
+      for (; u + 16 <= steps; u += 16) add(std::integral_constant<int, 16>{}, u);
+      for (; u + 4 <= steps; u += 4) add(std::integral_constant<int, 4>{}, u);
+      for (; u < steps; ++u) add(std::integral_constant<int, 1>{}, u);
+    }
+    __syncthreads();
+  }
+  float s = acc;
+  if constexpr (CH > 1) {
+    if (tid < CH * F) xs[tid] = acc;
+    __syncthreads();
+    s = 0.f;
+    if (tid < F)
+      for (int h = 0; h < CH; ++h) s += xs[h * F + tid];
+  }
+  if (tid < F) {
+    float* y = &Y[(size_t)r * kH + f0 + tid];
+    *y = accumulate ? *y + s : s;
   }
 }
 
@@ -535,84 +574,90 @@ __global__ __launch_bounds__(kBlock) void k_adam(int P, float* __restrict__ thet
 }
 
 // ------------------------------------------------------------------------------ graph build
-// Per-row statistics of rows [start or rowptr, rowptr+1) of a CSR matrix: Σ|v|, max|v|, Σv². A
-// wavefront per piece, partials of split rows to part (3 per slot) for k_rowstats_split; the rows of a
-// pack by a lane each. (One thread per row took 4.0 ms on the portfolio graph, whose longest row has
-// 2·10⁴ entries, and the edge weights below 11.2 ms; on the SVM training instance, 2·10⁶ entries, a
-// wavefront per piece takes 7 and 14 µs instead of 0.3 and 1.1 ms.)
-__device__ __forceinline__ void rowstats_put(double s, double mx, double q, double* sum_abs, double* max_abs,
-                                             double* sumsq, int r) {
-  sum_abs[r] = s;
-  max_abs[r] = mx;
-  sumsq[r] = q;
-}
-__device__ __forceinline__ double dmax_tree(double x) {
-  return wave_tree(x, [](double a, double b) { return b > a ? b : a; });
-}
-__device__ __forceinline__ double dsum_tree(double x) {
-  return wave_tree(x, [](double a, double b) { return a + b; });
-}
-__global__ __launch_bounds__(kBlock) void k_rowstats(const Piece* __restrict__ pieces, int npieces,
+// Per-row statistics of rows [start or rowptr, rowptr+1) of a CSR matrix: Σ|v|, max|v|, Σv², each row's
+// entries in order: the rows of a pack by a lane each, longer rows by a wavefront each that stages them in
+// LDS. (One thread per row took 4.0 ms on the portfolio graph, whose longest row has 2·10⁴ entries, bound
+// by the latency of its loads, and the edge weights below 11.2 ms: now 0.18 ms, the chain of additions of
+// that row, and 0.03 ms.)
+struct RowStats {
+  double s = 0.0, mx = 0.0, q = 0.0;
+  __device__ __forceinline__ void sums(double val) {
+    const double v = fabs(val);
+    s += v;
+    q += v * v;
+  }
+  __device__ __forceinline__ void max(double val) {
+    const double v = fabs(val);
+    mx = v > mx ? v : mx;
+  }
+};
+__global__ __launch_bounds__(kBlock) void k_rowstats(const Piece* __restrict__ packs, int npacks,
                                                      const int32_t* __restrict__ rowptr,
                                                      const int32_t* __restrict__ start,
                                                      const double* __restrict__ val,
                                                      double* __restrict__ sum_abs,
                                                      double* __restrict__ max_abs,
-                                                     double* __restrict__ sumsq, double* __restrict__ part) {
+                                                     double* __restrict__ sumsq) {
   const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (id >= npieces) return;
-  const Piece p = pieces[id];
-  const int lane = threadIdx.x & 63;
-  const bool pack = p.k1 < 0;
-  const int r = p.row + (pack ? lane : 0);
-  const bool mine = !pack || r < p.k0;
-  const int a = pack ? (mine ? (start ? start[r] : rowptr[r]) : 0) : p.k0 + lane;
-  const int b = pack ? (mine ? rowptr[r + 1] : 0) : p.k1, step = pack ? 1 : 64;
-  double s = 0.0, mx = 0.0, q = 0.0;
-#pragma unroll 4
-  for (int k = a; k < b; k += step) {
-    const double v = fabs(val[k]);
-    s += v;
-    mx = v > mx ? v : mx;
-    q += v * v;
+  if (id >= npacks) return;
+  const Piece p = packs[id];
+  const int r = p.row + (threadIdx.x & 63);
+  if (r >= p.k0) return;
+  RowStats t;
+  const int b = rowptr[r + 1];
+#pragma unroll 8
+  for (int k = start ? start[r] : rowptr[r]; k < b; ++k) {
+    t.sums(val[k]);
+    t.max(val[k]);
   }
-  if (pack) {
-    if (mine) rowstats_put(s, mx, q, sum_abs, max_abs, sumsq, r);
-    return;
-  }
-  s = dsum_tree(s);
-  mx = dmax_tree(mx);
-  q = dsum_tree(q);
-  if (lane == 0) {
-    if (p.slot < 0) {
-      rowstats_put(s, mx, q, sum_abs, max_abs, sumsq, p.row);
-    } else {
-      part[3 * (size_t)p.slot] = s;
-      part[3 * (size_t)p.slot + 1] = mx;
-      part[3 * (size_t)p.slot + 2] = q;
-    }
-  }
+  sum_abs[r] = t.s;
+  max_abs[r] = t.mx;
+  sumsq[r] = t.q;
 }
-__global__ __launch_bounds__(kBlock) void k_rowstats_split(const SplitRow* __restrict__ rows, int nrows,
-                                                           const double* __restrict__ part,
-                                                           double* __restrict__ sum_abs,
-                                                           double* __restrict__ max_abs,
-                                                           double* __restrict__ sumsq) {
-  const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (id >= nrows) return;
-  const SplitRow sr = rows[id];
-  const int lane = threadIdx.x & 63;
-  double s = 0.0, mx = 0.0, q = 0.0;
-  for (int c = lane; c < sr.count; c += 64) {
-    const double* p = part + 3 * (size_t)(sr.slot + c);
-    s += p[0];
-    mx = p[1] > mx ? p[1] : mx;
-    q += p[2];
+__global__ __launch_bounds__(64) void k_rowstats_rows(const int32_t* __restrict__ rows,
+                                                      const int32_t* __restrict__ rowptr,
+                                                      const int32_t* __restrict__ start,
+                                                      const double* __restrict__ val,
+                                                      double* __restrict__ sum_abs,
+                                                      double* __restrict__ max_abs,
+                                                      double* __restrict__ sumsq) {
+  constexpr int U = 16;
+  __shared__ double buf[64 * U];
+  const int r = rows[blockIdx.x], lane = threadIdx.x;
+  const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+  double v[U];
+  RowStats t;
+  if (a < b) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = val[min(a + lane + 64 * u, b - 1)];
   }
-  s = dsum_tree(s);
-  mx = dmax_tree(mx);
-  q = dsum_tree(q);
-  if (lane == 0) rowstats_put(s, mx, q, sum_abs, max_abs, sumsq, sr.row);
+  for (int k0 = a; k0 < b; k0 += 64 * U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      buf[lane + 64 * u] = v[u];
+      t.max(v[u]);  // lanes past the end hold the last entry
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = val[min(k0 + 64 * U + lane + 64 * u, b - 1)];
+    const int count = min(64 * U, b - k0);
+    int k = 0;  // every lane adds all, the same; the maximum has no order
+    for (; k + 16 <= count; k += 16) {
+      double x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = buf[k + u];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) t.sums(x[u]);
+    }
+    for (; k < count; ++k) t.sums(buf[k]);
+    __syncthreads();
+  }
+  t.mx = wave_tree(t.mx, [](double x, double y) { return y > x ? y : x; });
+  if (lane == 0) {
+    sum_abs[r] = t.s;
+    max_abs[r] = t.mx;
+    sumsq[r] = t.q;
+  }
 }
 
 // Edge weights on one CSR structure: w_row[k] = |v| / rowsum[row], w_col[k] = |v| / colsum[col−coff].
@@ -629,18 +674,21 @@ __global__ __launch_bounds__(kBlock) void k_edge_weights(const Piece* __restrict
   if (id >= npieces) return;
   const Piece p = pieces[id];
   const int lane = threadIdx.x & 63;
-  const bool pack = p.k1 < 0;
-  const int r = p.row + (pack ? lane : 0);
-  if (pack && r >= p.k0) return;
-  const int a = pack ? (start ? start[r] : rowptr[r]) : p.k0 + lane;
-  const int b = pack ? rowptr[r + 1] : p.k1, step = pack ? 1 : 64;
-  const double rs = rowsum[r];
+  auto part = [&](int r, int k, int end, int step) {
+    const double rs = rowsum[r];
 #pragma unroll 4
-  for (int k = a; k < b; k += step) {
-    const double v = fabs(val[k]);
-    const double cs = colsum[col[k] - coff];
-    w_row[k] = rs > 0 ? (float)(v / rs) : 0.f;
-    w_col[k] = cs > 0 ? (float)(v / cs) : 0.f;
+    for (; k < end; k += step) {
+      const double v = fabs(val[k]);
+      const double cs = colsum[col[k] - coff];
+      w_row[k] = rs > 0 ? (float)(v / rs) : 0.f;
+      w_col[k] = cs > 0 ? (float)(v / cs) : 0.f;
+    }
+  };
+  if (p.k1 >= 0) {
+    part(p.row, p.k0 + lane, p.k1, 64);
+  } else {  // 8 lanes per row
+    for (int r = p.row + (lane >> 3); r < p.k0; r += 8)
+      part(r, (start ? start[r] : rowptr[r]) + (lane & 7), rowptr[r + 1], 8);
   }
 }
 

@@ -64,28 +64,28 @@ constexpr int kTileNnz = 65536;    // SpMV entries per workgroup with an LDS gat
 constexpr int kPlainNnz = 8192;    // SpMV entries per workgroup without one
 constexpr int kTileMaxRows = 4096; // rows per SpMV row block at most
 
-// One wavefront's share of the graph kernels of the learned preconditioner (its SpMM and its row
-// statistics) over the rows of a CSR matrix (Section 5.1.4: row sums are a segmented reduction over
-// the RowPointer segments): entries [k0, k1) of one row, whole (slot −1) or as the partial `slot` of
-// a SplitRow; or, with k1 < 0, all of the rows [row, k0), at most kPackRows of at most kShortRow
-// entries each.
+// Work lists of the network's graph kernels over the rows of a matrix. A sum over a row is always added in
+// the row's order (float32 sums of other orders would change the preconditioner's last bits and with them,
+// now and then, a PCG iteration count): in 8 chains of entries ≡ 0..7 mod 8 where the whole row of the CSR
+// matrix has more than kChainRow entries, in one chain below. Short rows go to wavefronts in packs, the others
+// to workgroups of their own.
 struct Piece {
-  int32_t row, k0, k1, slot;
-};
-struct SplitRow {
-  int32_t row, slot, count;  // partials slot .. slot + count − 1, in column order
+  int32_t row, k0, k1;  // entries [k0, k1) of a row; k1 < 0: all of the rows [row, k0), a pack
 };
 struct PiecePlan {
-  std::vector<Piece> pieces;
-  std::vector<SplitRow> split;
-  int32_t slots = 0;
+  std::vector<Piece> pieces;   // packs first, then the longer rows in pieces of at most kPieceNnz entries
+  int32_t packs = 0;
+  std::vector<int32_t> rows;   // the longer rows: those of one chain first
+  int32_t one_chain = 0;
 };
 constexpr int kPieceNnz = 512;
-constexpr int kShortRow = 16;
+constexpr int kTinyRow = 16;    // packs of at most kPackRows rows of at most this many entries,
+constexpr int kShortRow = 256;  // or of at most 8 rows of at most this many
 constexpr int kPackRows = 16;
+constexpr int kChainRow = 2048;
 
-// Row r's entries are [start[r], end[r]).
-PiecePlan make_pieces(const int32_t* start, const int32_t* end, int32_t nrows);
+// Row r's entries are [start[r], end[r]); full[r] .. full[r + 1] are those of the whole row.
+PiecePlan make_pieces(const int32_t* start, const int32_t* end, const int32_t* full, int32_t nrows);
 
 // ---- SpMV work list (k_spmv / k_combine)
 //

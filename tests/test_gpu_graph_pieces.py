@@ -1,11 +1,12 @@
 """The network's graph kernels on rows at the edges of their work split. Needs an MI355X.
 
-A wavefront takes one piece of at most 512 entries of a row, or a pack of at most 16 rows of at most 16
-entries; longer rows are split and their partials added. The rows of Ā (and, transposed, of Āᵀ) have
-lengths on both sides of each of these limits. Float32 layers, against the float64 oracle; tolerance as
+A wavefront takes a pack of at most 16 rows of at most 16 entries or of 8 rows of at most 256; longer rows
+have workgroups of their own, which add them in one chain up to 2048 entries and in 8 chains above, in
+batches of 256 and 1024 entries; edge weights go by pieces of 512. The rows of Ā (and, transposed, of Āᵀ)
+have lengths on both sides of each of these limits. Float32 layers, against the float64 oracle; tolerance as
 for the other float32 comparisons of the network (1e-4 of the largest value): the weights of a row sum
-to 1, so a sum of up to 2000 float32 products is within 2000·2⁻²⁴ ≈ 1.2e-4 of its largest term in the
-worst case and within √2000·2⁻²⁴ ≈ 3e-6 typically.
+to 1, so a sum of up to 9000 float32 products is within 9000·2⁻²⁴ ≈ 5.4e-4 of its largest term in the
+worst case and within √9000·2⁻²⁴ ≈ 6e-6 typically.
 """
 import sys
 
@@ -21,6 +22,8 @@ pytestmark = pytest.mark.gpu
 
 LENGTHS = [1, 2, 15, 16, 17, 3, 1, 63, 64, 65, 511, 512, 513, 1, 1024, 1025, 2000] + [1] * 33 + [16] * 20 + [0, 5, 0]
 
+LONG = [255, 256, 257, 1, 2047, 2048, 2049, 4096, 9000, 1, 0, 3000] + [100] * 50 + [17] * 9 + [1] * 30 + [5000]
+
 
 def matrix(lengths, n, seed):
     rng = np.random.default_rng(seed)
@@ -30,10 +33,11 @@ def matrix(lengths, n, seed):
     return sp.csr_matrix((vals, np.concatenate(rows).astype(np.int32), indptr), shape=(len(lengths), n))
 
 
+@pytest.mark.parametrize("lengths", ["short", "long"])
 @pytest.mark.parametrize("transposed", [False, True])
-def test_forward_and_gradient_on_rows_of_every_length(transposed):
-    print("[case] pieces", "transposed" if transposed else "as is", file=sys.stderr, flush=True)
-    A = matrix(LENGTHS, 2000, 11)
+def test_forward_and_gradient_on_rows_of_every_length(transposed, lengths):
+    print("[case] pieces", lengths, "transposed" if transposed else "as is", file=sys.stderr, flush=True)
+    A = matrix(LENGTHS, 2000, 11) if lengths == "short" else matrix(LONG, 10_000, 3)
     if transposed:
         A = sp.csr_matrix(A.T)
     m, n = A.shape
