@@ -31,7 +31,7 @@ struct qpg_net {
 namespace qpg {
 
 struct LearnedState {
-  std::vector<void*> allocs;
+  DeviceArena arena;
   int n = 0, m = 0;
   float *fv = nullptr, *fc = nullptr;
   float *wA_hat = nullptr, *wA_chk = nullptr;  // on the Ā structure
@@ -69,18 +69,12 @@ struct LearnedState {
 
   template <typename T>
   T* alloc(size_t count) {
-    void* p = nullptr;
-    if (count == 0) count = 1;
-    hipError_t e = hipMalloc(&p, count * sizeof(T));
-    if (e != hipSuccess) throw HipError{e, "hipMalloc (learned preconditioner)"};
-    allocs.push_back(p);
-    return static_cast<T*>(p);
+    return static_cast<T*>(arena.get(count * sizeof(T), "hipMalloc (learned preconditioner)"));
   }
 };
 
 void destroy_learned(LearnedState* L) {
   if (!L) return;
-  for (void* p : L->allocs) (void)hipFree(p);
   if (L->ns_host) (void)hipHostFree(L->ns_host);
   if (L->mread) (void)hipHostFree(L->mread);
   delete L;
@@ -477,7 +471,7 @@ bool ensure_multi(qpg_solver* h, LearnedState* L) {
     return false;
   }
   HIPCHK(e);
-  L->allocs.push_back(p);
+  L->arena.own.push_back(p);
   L->mx = (MultiVec*)p;
   L->mr = L->mx + n;
   L->mkp = L->mr + n;

@@ -134,33 +134,25 @@ void qpg_solver::place_raw(const HostProblem& H) {
   const size_t nnz_a = H.a_src.size(), nnz_b = H.b_col.size();
   V.a_val = alloc<double>(nnz_a);
   V.b_val = alloc<double>(nnz_b);
-  std::vector<void*> tmp;
+  DeviceArena tmp;  // freed on return, after the synchronisation
   auto tmp_copy = [&](const void* src, size_t bytes) {
-    void* d = nullptr;
-    HIPCHK(hipMalloc(&d, std::max<size_t>(bytes, 1)));
-    tmp.push_back(d);
+    void* d = tmp.get(bytes, "hipMalloc");
     copy_h2d(d, src, bytes);
     return d;
   };
-  try {
-    const double* av = static_cast<const double*>(tmp_copy(H.a_csc_val, nnz_a * sizeof(double)));
-    const int32_t* src = static_cast<const int32_t*>(tmp_copy(H.a_src.data(), nnz_a * sizeof(int32_t)));
-    const int32_t* acp = static_cast<const int32_t*>(tmp_copy(H.a_colptr, ((size_t)n + 1) * sizeof(int32_t)));
-    const int32_t* pp = static_cast<const int32_t*>(tmp_copy(H.p_ptr.data(), ((size_t)n + 1) * sizeof(int32_t)));
-    const double* pv = static_cast<const double*>(tmp_copy(H.p_val.data(), H.p_val.size() * sizeof(double)));
-    if (nnz_a) {
-      const int g = (int)std::min<size_t>((nnz_a + kBlock - 1) / kBlock, 65536);
-      hipLaunchKernelGGL(k_gather_values, dim3(g), dim3(kBlock), 0, stream, (int64_t)nnz_a, src, av, V.a_val);
-    }
-    const int gb = std::max(1, std::min((n + 3) / 4, 16384));
-    hipLaunchKernelGGL(k_assemble_b, dim3(gb), dim3(kBlock), 0, stream, n, (const int32_t*)b_ptr,
-                       (const int32_t*)b_split, pp, pv, acp, av, V.b_val);
-    HIPCHK(hipStreamSynchronize(stream));
-  } catch (...) {
-    for (void* d : tmp) (void)hipFree(d);
-    throw;
+  const double* av = static_cast<const double*>(tmp_copy(H.a_csc_val, nnz_a * sizeof(double)));
+  const int32_t* src = static_cast<const int32_t*>(tmp_copy(H.a_src.data(), nnz_a * sizeof(int32_t)));
+  const int32_t* acp = static_cast<const int32_t*>(tmp_copy(H.a_colptr, ((size_t)n + 1) * sizeof(int32_t)));
+  const int32_t* pp = static_cast<const int32_t*>(tmp_copy(H.p_ptr.data(), ((size_t)n + 1) * sizeof(int32_t)));
+  const double* pv = static_cast<const double*>(tmp_copy(H.p_val.data(), H.p_val.size() * sizeof(double)));
+  if (nnz_a) {
+    const int g = (int)std::min<size_t>((nnz_a + kBlock - 1) / kBlock, 65536);
+    hipLaunchKernelGGL(k_gather_values, dim3(g), dim3(kBlock), 0, stream, (int64_t)nnz_a, src, av, V.a_val);
   }
-  for (void* d : tmp) HIPCHK(hipFree(d));
+  const int gb = std::max(1, std::min((n + 3) / 4, 16384));
+  hipLaunchKernelGGL(k_assemble_b, dim3(gb), dim3(kBlock), 0, stream, n, (const int32_t*)b_ptr,
+                     (const int32_t*)b_split, pp, pv, acp, av, V.b_val);
+  HIPCHK(hipStreamSynchronize(stream));
 }
 
 // FP32 copies of the equilibrated device data (matrix values in CSR; the SELL copies are placed
