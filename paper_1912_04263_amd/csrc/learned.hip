@@ -246,7 +246,7 @@ void spmm(qpg_solver* h, const LearnedState::List& l, const int32_t* ptr, const 
     hipLaunchKernelGGL((k_spmm_rows<1, 32>), dim3(l.one_chain), dim3(kSpmmBlock), 0, h->stream,
                        (const int32_t*)l.rows, ptr, start, col, w, coff, X, Y, acc);
   if (l.nrows > l.one_chain)
-    hipLaunchKernelGGL((k_spmm_rows<8, 8>), dim3((l.nrows - l.one_chain) * (kH / 8)), dim3(kSpmmBlock), 0, h->stream,
+    hipLaunchKernelGGL((k_spmm_rows<8, 16>), dim3((l.nrows - l.one_chain) * (kH / 16)), dim3(kSpmmBlock), 0, h->stream,
                        (const int32_t*)l.rows + l.one_chain, ptr, start, col, w, coff, X, Y, acc);
 }
 void spmm_A(qpg_solver* h, const float* w, const float* X, float* Y, int acc) {

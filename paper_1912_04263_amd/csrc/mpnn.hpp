@@ -72,7 +72,7 @@ __device__ __forceinline__ float softplusf(float g) { return fmaxf(g, 0.f) + log
 // rowptr[r]) to rowptr[r+1]; 32 features, each row's products added in its order (PiecePlan).
 
 // Packs of short rows: a wavefront per pack, 8 lanes per row with its 32 features as float4 (one 128-byte
-// row of X per entry), 8 or 4 entries in flight. Bound by the latency of the gathers that follow one another.
+// row of X per entry), 12 or 4 entries in flight. Bound by the latency of the gathers that follow one another.
 template <int U>
 __device__ __forceinline__ float4 spmm_row(const int32_t* __restrict__ col, const float* __restrict__ w, int coff,
                                            const float* __restrict__ X, int a, int b, int f) {
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm32(const Piece* __restrict__ pac
   const int lane = threadIdx.x & 63, f = 4 * (lane & 7);
   for (int r = p.row + (lane >> 3); r < p.k0; r += 8) {
     const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
-    const float4 v = b - a > 4 ? spmm_row<8>(col, w, coff, X, a, b, f) : spmm_row<4>(col, w, coff, X, a, b, f);
+    const float4 v = b - a > 16 ? spmm_row<12>(col, w, coff, X, a, b, f) : spmm_row<4>(col, w, coff, X, a, b, f);
     float4* y = reinterpret_cast<float4*>(&Y[(size_t)r * kH + f]);
     const float4 o = accumulate ? *y : float4{0.f, 0.f, 0.f, 0.f};
     *y = accumulate ? float4{o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w} : v;
@@ -120,8 +120,8 @@ __global__ __launch_bounds__(kBlock) void k_spmm32(const Piece* __restrict__ pac
 // Longer rows: a workgroup per row and F of its features. All 512 threads gather a batch of entries into
 // LDS, the next one's loads in flight meanwhile; CH·F lanes then add it, lane (g, f) the entries ≡ g mod
 // CH of feature f in order. On the portfolio graph (rows of 10⁴ and 2·10⁴ entries) one workgroup per row that
-// gathered as it added took 282 µs on average (525 at most); now 60 µs, bound by the chain of 2500 additions
-// of the longest row. Splitting such rows into pieces took 24 µs, but adds in another order.
+// gathered as it added took 282 µs on average (525 at most); now 49 µs with 16 features per workgroup, bound
+// by the batches of the longest row that follow one another (8 features: 60 µs, for 4 times the requests). Splitting such rows into pieces took 24 µs, but adds in another order.
 constexpr int kSpmmBlock = 512;
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 template <int CH, int F>
