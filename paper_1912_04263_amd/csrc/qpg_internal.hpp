@@ -177,6 +177,14 @@ struct TileParams {
 TilePlan make_tiles(const std::vector<int32_t>& rowptr, const int32_t* col, int32_t nrows, int32_t ncols,
                     const TileParams& tp);
 
+// Whether every row has exactly one segment, so that segment r in row order is row r's. Their number alone
+// does not tell: an empty row has none and a long row several, and the counts may cancel.
+inline bool segments_are_rows(const TilePlan& t) {
+  for (size_t r = 0; r < t.rowslot.size(); ++r)
+    if (t.rowslot[r] != (int32_t)r) return false;
+  return true;
+}
+
 // ---- host parallelism for setup
 // f(c, lo, hi) for the chunks [c·chunk, min(n, (c+1)·chunk)) of [0, n), on up to 16 threads.
 // The chunking does not depend on the thread count, so results that combine per-chunk partials

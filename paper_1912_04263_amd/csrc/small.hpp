@@ -51,6 +51,7 @@ struct SmallMat {
   const uint16_t *segslot, *rowslot, *col;  // segslot 65535: an empty lane
   const T* val;
   int32_t nchunk, nitem, nslot, nval, nrows;
+  int32_t rows;  // segments_are_rows
 };
 
 // How the right-hand side of a launch's first iteration is formed (qpg_solver::admm): directly, by
@@ -114,7 +115,7 @@ struct SmallCtx {
   SmallLds o;
   int32_t n, m, vgrid, maxit;
   int32_t nchunk[2], nitem[2], nslot[2];
-  bool rows_A;  // Ā has one segment per row: a slot is a row, no sums of slots to wait for
+  bool rows_A;  // each row of Ā has one segment: a slot is a row, no sums of slots to wait for
   const T* val[2];
   const uint16_t* col[2];
   T sigma, alpha, rho, rho_inv;
@@ -133,7 +134,7 @@ struct SmallCtx {
     nitem[1] = a.B.nitem;
     nslot[0] = a.A.nslot;
     nslot[1] = a.B.nslot;
-    rows_A = a.A.nslot == a.A.nrows;
+    rows_A = a.A.rows != 0;
     val[0] = a.A.val;
     val[1] = a.B.val;
     col[0] = a.A.col;

@@ -262,6 +262,7 @@ SmallArgs<T> qpg_solver::small_args(double rho) {
     M.nslot = (int32_t)pl.nslot;
     M.nval = (int32_t)pl.nsrc;
     M.nrows = pl.nrows;
+    M.rows = pl.s_rows;
     return M;
   };
   a.A = mat(plan_a);
@@ -1124,6 +1125,7 @@ void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t
     pl.s_items = upload(s_items);
     pl.s_segslot = upload(s_segslot);
     pl.s_rowslot = upload(s_rowslot);
+    pl.s_rows = segments_are_rows(t);
     pl.s_col = alloc<uint16_t>((size_t)t.n_src);
     if (pl.nchunk)
       hipLaunchKernelGGL(k_small_cols, dim3(pl.nchunk), dim3(kBlock), 0, stream, pl.nchunk, (const Chunk*)pl.chunks,

@@ -153,6 +153,7 @@ struct DevPlan {
   SmallChunk* s_chunks = nullptr;
   SmallItem* s_items = nullptr;
   uint16_t *s_segslot = nullptr, *s_rowslot = nullptr, *s_col = nullptr;
+  bool s_rows = false;  // segments_are_rows
   int32_t nchunk = 0;
   int32_t* src = nullptr;  // CSR index of every SELL position, on the device until the values are placed
   int64_t nsrc = 0;
