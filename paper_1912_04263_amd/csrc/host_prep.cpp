@@ -262,7 +262,7 @@ PiecePlan make_pieces(const int32_t* start, const int32_t* end, const int32_t* f
   p.one_chain = (int32_t)p.rows.size();
   p.rows.insert(p.rows.end(), chained.begin(), chained.end());
   for (int32_t r : p.rows) {  // near-equal pieces
-    const int32_t count = (len(r) + kPieceNnz - 1) / kPieceNnz;
+    const int32_t count = len(r) / kPieceNnz + (len(r) % kPieceNnz != 0);
     for (int32_t c = 0; c < count; ++c)
       p.pieces.push_back({r, start[r] + (int32_t)((int64_t)len(r) * c / count),
                           start[r] + (int32_t)((int64_t)len(r) * (c + 1) / count)});

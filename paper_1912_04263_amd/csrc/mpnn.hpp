@@ -75,14 +75,14 @@ __device__ __forceinline__ float softplusf(float g) { return fmaxf(g, 0.f) + log
 // row of X per entry), 12 or 4 entries in flight. Bound by the latency of the gathers that follow one another.
 template <int U>
 __device__ __forceinline__ float4 spmm_row(const int32_t* __restrict__ col, const float* __restrict__ w, int coff,
-                                           const float* __restrict__ X, int a, int b, int f) {
+                                           const float* __restrict__ X, uint32_t a, uint32_t b, int f) {
   float4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = a; k0 < b; k0 += U) {
+  for (uint32_t k0 = a; k0 < b; k0 += U) {
     float wk[U];
     float4 x[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {  // past the end: the row's last entry, not added
-      const int k = min(k0 + u, b - 1);
+      const uint32_t k = entry_ahead(k0, u, b - 1);
       wk[u] = w[k];
       x[u] = *reinterpret_cast<const float4*>(&X[(size_t)(col[k] - coff) * kH + f]);
     }
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm32(const Piece* __restrict__ pac
   const Piece p = packs[id];
   const int lane = threadIdx.x & 63, f = 4 * (lane & 7);
   for (int r = p.row + (lane >> 3); r < p.k0; r += 8) {
-    const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+    const uint32_t a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
     const float4 v = b - a > 16 ? spmm_row<12>(col, w, coff, X, a, b, f) : spmm_row<4>(col, w, coff, X, a, b, f);
     float4* y = reinterpret_cast<float4*>(&Y[(size_t)r * kH + f]);
     const float4 o = accumulate ? *y : float4{0.f, 0.f, 0.f, 0.f};
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kSpmmBlock, 8) void k_spmm_rows(const int32_t* __re
   __shared__ __align__(16) float xs[E * F];
   __shared__ float ws[E];
   const int r = rows[blockIdx.x / (kH / F)], f0 = (blockIdx.x % (kH / F)) * F;
-  const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+  const uint32_t a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
   const int tid = threadIdx.x, le = tid / LP, lf = 4 * (tid % LP);
   if (a >= b) {  // (uniform in the workgroup)
     if (tid < F && !accumulate) Y[(size_t)r * kH + f0 + tid] = 0.f;
@@ -151,15 +151,15 @@ __global__ __launch_bounds__(kSpmmBlock, 8) void k_spmm_rows(const int32_t* __re
   float wk[W];
   int c[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) c[u] = col[min(a + le + u * S, b - 1)];
+  for (int u = 0; u < U; ++u) c[u] = col[entry_ahead(a, le + u * S, b - 1)];
 #pragma unroll
   for (int u = 0; u < U; ++u) x[u] = *reinterpret_cast<const floatx4*>(&X[(size_t)(c[u] - coff) * kH + f0 + lf]);
 #pragma unroll
-  for (int u = 0; u < W; ++u) wk[u] = w[min(a + tid + u * kSpmmBlock, b - 1)];
+  for (int u = 0; u < W; ++u) wk[u] = w[entry_ahead(a, tid + u * kSpmmBlock, b - 1)];
 #pragma unroll
-  for (int u = 0; u < U; ++u) c[u] = col[min(a + E + le + u * S, b - 1)];
+  for (int u = 0; u < U; ++u) c[u] = col[entry_ahead(a, E + le + u * S, b - 1)];
   float acc = 0.f;
-  for (int k0 = a; k0 < b; k0 += E) {
+  for (uint32_t k0 = a; k0 < b; k0 += E) {
 #pragma unroll
     for (int u = 0; u < U; ++u) *reinterpret_cast<floatx4*>(&xs[(le + u * S) * F + lf]) = x[u];
 #pragma unroll
@@ -169,11 +169,11 @@ __global__ __launch_bounds__(kSpmmBlock, 8) void k_spmm_rows(const int32_t* __re
 #pragma unroll
     for (int u = 0; u < U; ++u) x[u] = *reinterpret_cast<const floatx4*>(&X[(size_t)(c[u] - coff) * kH + f0 + lf]);
 #pragma unroll
-    for (int u = 0; u < W; ++u) wk[u] = w[min(k0 + E + tid + u * kSpmmBlock, b - 1)];
+    for (int u = 0; u < W; ++u) wk[u] = w[entry_ahead(k0, E + tid + u * kSpmmBlock, b - 1)];
 #pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = col[min(k0 + 2 * E + le + u * S, b - 1)];
+    for (int u = 0; u < U; ++u) c[u] = col[entry_ahead(k0, 2 * E + le + u * S, b - 1)];
     if (tid < CH * F) {
-      const int count = min(E, b - k0), g = tid / F, steps = (count - g + CH - 1) / CH;
+      const int count = (int)min((uint32_t)E, b - k0), g = tid / F, steps = (count - g + CH - 1) / CH;
       auto add = [&](auto many, int u0) {
         constexpr int M = decltype(many)::value;
         float wv[M], xv[M];
@@ -624,14 +624,14 @@ __global__ __launch_bounds__(64) void k_rowstats_rows(const int32_t* __restrict_
   constexpr int U = 16;
   __shared__ double buf[64 * U];
   const int r = rows[blockIdx.x], lane = threadIdx.x;
-  const int a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
+  const uint32_t a = start ? start[r] : rowptr[r], b = rowptr[r + 1];
   double v[U];
   RowStats t;
   if (a < b) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = val[min(a + lane + 64 * u, b - 1)];
+    for (int u = 0; u < U; ++u) v[u] = val[entry_ahead(a, lane + 64 * u, b - 1)];
   }
-  for (int k0 = a; k0 < b; k0 += 64 * U) {
+  for (uint32_t k0 = a; k0 < b; k0 += 64 * U) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       buf[lane + 64 * u] = v[u];
@@ -639,8 +639,8 @@ __global__ __launch_bounds__(64) void k_rowstats_rows(const int32_t* __restrict_
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = val[min(k0 + 64 * U + lane + 64 * u, b - 1)];
-    const int count = min(64 * U, b - k0);
+    for (int u = 0; u < U; ++u) v[u] = val[entry_ahead(k0, 64 * U + lane + 64 * u, b - 1)];
+    const int count = (int)min(64u * U, b - k0);
     int k = 0;  // every lane adds all, the same; the maximum has no order
     for (; k + 16 <= count; k += 16) {
       double x[16];
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(kBlock) void k_edge_weights(const Piece* __restrict
   if (id >= npieces) return;
   const Piece p = pieces[id];
   const int lane = threadIdx.x & 63;
-  auto part = [&](int r, int k, int end, int step) {
+  auto part = [&](int r, uint32_t k, uint32_t end, int step) {
     const double rs = rowsum[r];
 #pragma unroll 4
     for (; k < end; k += step) {

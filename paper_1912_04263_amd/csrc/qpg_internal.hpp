@@ -84,6 +84,10 @@ constexpr int kShortRow = 256;  // or of at most 8 rows of at most this many
 constexpr int kPackRows = 16;
 constexpr int kChainRow = 2048;
 
+// Entry k + by of a row, or its last one where that lies past the end. Unsigned, also the loops over k: a row may
+// end within `by` of 2³¹ − 1, where an int32 sum would wrap to a negative index.
+constexpr uint32_t entry_ahead(uint32_t k, uint32_t by, uint32_t last) { return k + by < last ? k + by : last; }
+
 // Row r's entries are [start[r], end[r]); full[r] .. full[r + 1] are those of the whole row.
 PiecePlan make_pieces(const int32_t* start, const int32_t* end, const int32_t* full, int32_t nrows);
 
