@@ -186,7 +186,8 @@ __device__ __forceinline__ double wave_reduce(int s, double x) {
 // The trees of NS slots at once. At each of the first steps a lane hands one half of its slots to its
 // partner and takes the partner's other half, so a step costs half of the one before (for 8 slots 10
 // combinations instead of 48); every slot is still combined by its own tree above. The result of slot s
-// is in lane s·kSlotLanes<NS>; all 64 lanes active.
+// is in lane s·kSlotLanes<NS>; all 64 lanes active. With 8 (padded) slots, slots 2j and 2j + 1 are both sums or
+// both maxima: at offset 16 a lane still holds one of each such pair while comb_lane goes by its final slot.
 template <int NS>
 constexpr int kSlotPad = NS > 4 ? 8 : NS > 2 ? 4 : NS;  // 1, 2, 4 or 8
 template <int NS>
@@ -208,6 +209,7 @@ __device__ __forceinline__ double comb_lane(int, int lane, double a, double b) {
 template <int NS, unsigned MAXMASK>
 __device__ __forceinline__ double wave_reduce_slots(const double (&v)[NS]) {
   constexpr int P = kSlotPad<NS>;
+  static_assert(P < 8 || ((MAXMASK ^ (MAXMASK >> 1)) & 0x55u) == 0, "slots 2j and 2j + 1: both sums or both maxima");
   double x[P];
 #pragma unroll
   for (int s = 0; s < P; ++s) x[s] = s < NS ? v[s < NS ? s : 0] : 0.0;
