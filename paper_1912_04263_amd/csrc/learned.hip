@@ -92,12 +92,9 @@ int div_up(long a, long b) { return (int)((a + b - 1) / b); }
 constexpr int kGradRows = 96;
 constexpr int kGradGroups = 512;
 
-// Build the graph data of the scaled problem once: row statistics of Ā and Āᵀ, normalised
-// edge weights on both CSR structures, node features; allocate activations.
-LearnedState* ensure_graph(qpg_solver* h) {
-  if (h->learned) return h->learned;
-  LearnedState* L = new LearnedState();
-  h->learned = L;
+// The graph data of the scaled problem: row statistics of Ā and Āᵀ, normalised
+// edge weights on both CSR structures, node features; and the activations.
+void build_graph(qpg_solver* h, LearnedState* L) {
   const int n = h->n, m = h->m;
   L->n = n;
   L->m = m;
@@ -194,7 +191,14 @@ LearnedState* ensure_graph(qpg_solver* h) {
   L->acc = L->alloc<double>(n);
   L->probe = L->alloc<int8_t>((size_t)kMulti * n);
   HIPCHK(hipGetLastError());
-  return L;
+}
+
+LearnedState* ensure_graph(qpg_solver* h) {
+  return build_once(h->learned, [h](LearnedState* L) { build_graph(h, L); },
+                    [h](LearnedState* L) {
+                      (void)hipStreamSynchronize(h->stream);  // kernels on its arrays
+                      destroy_learned(L);
+                    });
 }
 
 void dense_fwd(qpg_solver* h, bool bf16, int N, const float* X1, const float* X2, const float* W,

@@ -58,6 +58,23 @@ struct NoInit : std::allocator<T> {
 template <class T>
 using hvec = std::vector<T, NoInit<T>>;
 
+// *slot, built on its first use: it is stored only once complete, and destroyed where building throws.
+template <class T, class Build, class Destroy>
+T* build_once(T*& slot, Build build, Destroy destroy) {
+  if (slot) return slot;
+  struct Owner {
+    T* p;
+    Destroy& destroy;
+    ~Owner() {
+      if (p) destroy(p);
+    }
+  } own{new T(), destroy};
+  build(own.p);
+  slot = own.p;
+  own.p = nullptr;
+  return slot;
+}
+
 constexpr double kInf = 1e20;       // |bound| ≥ kInf is infinite
 constexpr int kBlock = 256;         // threads per workgroup (4 wavefronts of 64)
 constexpr int kTileNnz = 65536;    // SpMV entries per workgroup with an LDS gather window
