@@ -62,7 +62,6 @@ struct LearnedState {
   MultiRead* mread = nullptr;  // mapped host memory
   MultiRead* mread_dev = nullptr;
   uint32_t mreads = 0;
-  int mlast = 1;  // PCG iterations of the last batch
   // inference network of the solve (settings.precond == QPG_PRECOND_LEARNED)
   float* theta_inf = nullptr;
   bool trunk_ready = false;
@@ -530,6 +529,7 @@ int hutchinson_multi(qpg_solver* h, LearnedState* L, const int8_t* signs, int32_
   h->fill(L->acc, n, 0.0);
   MultiVec* w = L->mp + n;
   const dim3 vg(h->vgrid), vb(kBlock);
+  int predicted = 1;  // nothing is carried over from an earlier call
   for (int k = 0; k < nprobes; k += kMulti) {
     const int count = std::min<int>(kMulti, nprobes - k);
     HIPCHK(hipMemcpyAsync(L->probe, signs + (size_t)k * n, (size_t)count * n, hipMemcpyHostToDevice, h->stream));
@@ -537,8 +537,8 @@ int hutchinson_multi(qpg_solver* h, LearnedState* L, const int8_t* signs, int32_
     multi_pass(h, L, h->plan_a, INT32_MAX, 1, L->mx, MultiScaled{w, rho});
     const MultiR0 r0{L->mx, L->probe, V.dinv, L->mr, L->mp, h->s.sigma, n, L->mst, max_iter};
     h->finalize(r0, multi_pass(h, L, h->plan_b, n, 2, L->mp, r0));
-    // iterations in batches, the first one as many as the last batch's solves took
-    int issued = 0, batch = std::max(1, std::min(L->mlast, max_iter));
+    // iterations between host reads: first as many as the call's last four solves took, then 2, 4, 8, 8, …
+    int issued = 0, batch = predicted, more = 1;
     for (;;) {
       const int b = std::min(batch, max_iter - issued);
       for (int i = 0; i < b; ++i) {
@@ -556,9 +556,9 @@ int hutchinson_multi(qpg_solver* h, LearnedState* L, const int8_t* signs, int32_
                          ++L->mreads);
       h->spin(&L->mread->seq, L->mreads);
       if (L->mread->all_done || issued >= max_iter) break;
-      batch = 8;
+      batch = more = std::min(2 * more, 8);
     }
-    L->mlast = std::max(1, L->mread->iter);
+    predicted = std::max(1, L->mread->iter);
     hipLaunchKernelGGL(k_multi_acc, vg, vb, 0, h->stream, n, count, (const int8_t*)L->probe, (const MultiVec*)L->mx,
                        L->acc);
   }
