@@ -257,6 +257,11 @@ int qpg_time_kernel(qpg_solver* h, int32_t kernel, int32_t precision, int32_t re
  * per launch (sum over tiles); out[6] segment slots; out[7] segment chunks. */
 int qpg_spmv_layout(const qpg_solver* h, int32_t matrix, int64_t out[8]);
 
+/* How the one-workgroup kernels (settings.speculate) take the problem in one arithmetic (QPG_FP64, QPG_MIXED for
+ * float), for tests and measurement: 0: not; 1: with work lists and PCG vectors in LDS; 2: and the ADMM vectors;
+ * 3: and the matrices. QPG_ERR_STATE for QPG_MIXED on a handle set up without it. */
+int qpg_small_level(const qpg_solver* h, int32_t precision, int32_t* level);
+
 /* K_ii = diag(P̄)_i + σ + ρ̄‖Ā_i‖² of the scaled reduced KKT matrix (Section 6.3.1), n values.
  * QPG_ERR_STATE for a handle set up with settings.rho_vector (K is taken with R = ρ̄I here). */
 int qpg_get_kdiag(const qpg_solver* h, double rho, double* kdiag);

@@ -1257,6 +1257,15 @@ int qpg_spmv_layout(const qpg_solver* h, int32_t matrix, int64_t out[8]) {
   return QPG_OK;
 }
 
+int qpg_small_level(const qpg_solver* h, int32_t precision, int32_t* level) {
+  if (!h || !level || (precision != QPG_FP64 && precision != QPG_MIXED)) return QPG_ERR_ARG;
+  if (precision == QPG_MIXED && !h->p32.ready) return QPG_ERR_STATE;
+  const SmallPlan& sp = precision == QPG_FP64 ? h->small64 : h->small32;
+  const bool on = precision == QPG_FP64 ? h->use_small<double>() : h->use_small<float>();
+  *level = !on ? 0 : sp.mats ? 3 : sp.vecs ? 2 : 1;
+  return QPG_OK;
+}
+
 int qpg_setup(qpg_solver** out, const qpg_csc* P_triu, const double* q, const qpg_csc* A,
               const double* l, const double* u, const qpg_settings* settings) {
   g_setup_error.clear();

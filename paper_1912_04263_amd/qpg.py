@@ -91,6 +91,7 @@ SIGNATURES = {
     "qpg_set_rho": (C.c_int, [C.c_void_p, C.c_double]),
     "qpg_time_kernel": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, _PD]),
     "qpg_spmv_layout": (C.c_int, [C.c_void_p, C.c_int32, C.POINTER(C.c_int64)]),
+    "qpg_small_level": (C.c_int, [C.c_void_p, C.c_int32, _PI]),
     "qpg_cleanup": (C.c_int, [C.c_void_p]),
     "qpg_get_kdiag": (C.c_int, [C.c_void_p, C.c_double, _PD]),
     "qpg_hutchinson": (C.c_int, [C.c_void_p, _PB, C.c_int32, C.c_double, C.c_double, C.c_int32, _PD]),
@@ -301,6 +302,13 @@ class Solver:
         keys = ("entries", "windowed_positions", "plain_positions", "tiles", "windowed_tiles",
                 "staged_columns", "slots", "chunks")
         return dict(zip(keys, (int(v) for v in out)))
+
+    def small_level(self, precision: int = QPG_FP64) -> int:
+        """How the one-workgroup kernels take the problem: 0 not, 1 with the PCG vectors in LDS, 2 with the
+        ADMM vectors too, 3 with the matrices too."""
+        level = C.c_int32()
+        self._check(lib().qpg_small_level(self._h, precision, C.byref(level)))
+        return level.value
 
     def kdiag(self, rho: float):
         out = np.empty(self.n)

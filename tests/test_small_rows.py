@@ -71,3 +71,8 @@ def test_random_rows(check):
         assert out["flag"] == out["entries"], seed
         cancel += out["segments"] == out["rows"] and not out["flag"]
     assert cancel > 0
+
+
+def test_level_of_no_handle():
+    from paper_1912_04263_amd import qpg
+    assert qpg.lib().qpg_small_level(None, qpg.QPG_FP64, None) == qpg.QPG_ERR_ARG
