@@ -262,6 +262,12 @@ int qpg_spmv_layout(const qpg_solver* h, int32_t matrix, int64_t out[8]);
  * 3: and the matrices. QPG_ERR_STATE for QPG_MIXED on a handle set up without it. */
 int qpg_small_level(const qpg_solver* h, int32_t precision, int32_t* level);
 
+/* Device memory that the handle holds, its network's graph included: out[0] bytes of allocations, out[1] of them in
+ * use (the rest are blocks that later requests are carved from). With FP64, 44 bytes per entry of A (columns twice,
+ * values in row order and as streamed, for A and for [P | A'], with 16-bit columns in windows and 4 more where there
+ * is none), and what goes by rows, columns and segments. */
+int qpg_device_bytes(const qpg_solver* h, int64_t out[2]);
+
 /* K_ii = diag(P̄)_i + σ + ρ̄‖Ā_i‖² of the scaled reduced KKT matrix (Section 6.3.1), n values.
  * QPG_ERR_STATE for a handle set up with settings.rho_vector (K is taken with R = ρ̄I here). */
 int qpg_get_kdiag(const qpg_solver* h, double rho, double* kdiag);

@@ -468,13 +468,14 @@ bool ensure_multi(qpg_solver* h, LearnedState* L) {
   }
   HIPCHK(hipHostGetDevicePointer((void**)&L->mread_dev, L->mread, 0));
   void* p = nullptr;
-  const hipError_t e = hipMalloc(&p, (4 * n + m + nslot) * sizeof(MultiVec) + sizeof(MultiState));
+  const size_t bytes = (4 * n + m + nslot) * sizeof(MultiVec) + sizeof(MultiState);
+  const hipError_t e = hipMalloc(&p, bytes);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     return false;
   }
   HIPCHK(e);
-  L->arena.own.push_back(p);
+  L->arena.adopt(p, bytes);
   L->mx = (MultiVec*)p;
   L->mr = L->mx + n;
   L->mkp = L->mr + n;
@@ -606,6 +607,17 @@ int qpg_get_kdiag(const qpg_solver* h, double rho, double* kdiag) {
   if (!h || !kdiag || !(rho > 0)) return QPG_ERR_ARG;
   if (h->s.rho_vector) return QPG_ERR_STATE;  // K is defined here with R = ρ̄I
   for (int i = 0; i < h->n; ++i) kdiag[i] = h->diagP_h[i] + h->s.sigma + rho * h->colsq_h[i];
+  return QPG_OK;
+}
+
+int qpg_device_bytes(const qpg_solver* h, int64_t out[2]) {
+  if (!h || !out) return QPG_ERR_ARG;
+  out[0] = (int64_t)h->arena.held;
+  out[1] = (int64_t)h->arena.used;
+  if (h->learned) {
+    out[0] += (int64_t)h->learned->arena.held;
+    out[1] += (int64_t)h->learned->arena.used;
+  }
   return QPG_OK;
 }
 

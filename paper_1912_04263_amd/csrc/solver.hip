@@ -1068,11 +1068,8 @@ TilePlan qpg_solver::plan_tiles(const std::vector<int32_t>& rowptr, const int32_
   return make_tiles(rowptr, col, nrows, ncols, tp);
 }
 
-// The work list on the device. The entries in SELL order (CSR index and column of every
-// position) are written there from the lanes and the pattern's columns dcol, already on the
-// device, instead of being built on the host and uploaded.
-void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t>& rowptr, int32_t nrows,
-                             const int32_t* dcol) {
+// The work list on the device, and room for the entries in SELL order.
+void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, int64_t nnz, int32_t nrows) {
   if (t.tiles.empty()) t.tiles.push_back(Tile{0, 0, 0, 0});
   if (t.comb.empty()) t.comb.push_back(CombItem{0, 0, 0, 0});
   pl.ncomb = (int32_t)t.comb.size();
@@ -1085,17 +1082,10 @@ void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t
   pl.slotidx = upload(t.slotidx);
   pl.tbase = upload(t.tbase);
   pl.nsrc = t.n_src;
-  pl.src = alloc<int32_t>((size_t)t.n_src);
   pl.col16 = alloc<uint16_t>((size_t)t.n_c16);
   pl.col32 = alloc<int32_t>((size_t)t.n_c32);
-  int32_t* lstart = upload(t.lstart);
-  int32_t* llen = upload(t.llen);
-  const int64_t nnz = (int64_t)rowptr[nrows] - rowptr[0];
-  const int g = std::max(1, std::min(pl.ntiles, 65536));
-  hipLaunchKernelGGL(k_sell_build, dim3(g), dim3(kBlock), 0, stream, (const Tile*)pl.tiles, pl.ntiles,
-                     (const Chunk*)pl.chunks, (int64_t)t.chunks.size(), (const int32_t*)lstart,
-                     (const int32_t*)llen, dcol, nnz, pl.src, t.n_src, pl.col16, t.n_c16, pl.col32, t.n_c32);
-  HIPCHK(hipGetLastError());
+  pl.val64 = alloc<double>((size_t)t.n_src);
+  if (s.precision == QPG_MIXED) pl.val32 = alloc<float>((size_t)t.n_src);
   pl.nchunk = (int32_t)t.chunks.size();
   pl.nslot = t.nslot;
   pl.nrows = nrows;
@@ -1103,16 +1093,11 @@ void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t
   std::vector<SmallChunk> s_chunks;
   std::vector<SmallItem> s_items;
   std::vector<uint16_t> s_segslot, s_rowslot;
-  std::vector<int32_t> wlo, inv;
+  std::vector<int32_t> inv;
   if (t.n_src * (int64_t)(sizeof(float) + sizeof(uint16_t)) <= kSmallBytes && n <= kSmallCols - m &&
       t.nslot < kSmallCols) {
     s_chunks.resize(t.chunks.size());
-    wlo.resize(t.chunks.size());
-    for (const Tile& x : t.tiles)
-      for (int32_t ci = x.chunk0; ci < x.chunk0 + x.nchunk; ++ci) {
-        s_chunks[ci] = SmallChunk{t.chunks[ci].base, t.chunks[ci].steps};
-        wlo[ci] = x.wlen > 0 ? x.wlo : -1;
-      }
+    for (size_t ci = 0; ci < t.chunks.size(); ++ci) s_chunks[ci] = SmallChunk{t.chunks[ci].base, t.chunks[ci].steps};
     for (const CombItem& c : t.comb) s_items.push_back({(uint16_t)c.r0, (uint16_t)c.r1, std::max(c.lg, 0)});
     inv.assign((size_t)t.nslot, 0);
     for (size_t q = 0; q < t.slotidx.size(); ++q) inv[t.slotidx[q]] = (int32_t)q;
@@ -1127,9 +1112,6 @@ void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t
     pl.s_rowslot = upload(s_rowslot);
     pl.s_rows = segments_are_rows(t);
     pl.s_col = alloc<uint16_t>((size_t)t.n_src);
-    if (pl.nchunk)
-      hipLaunchKernelGGL(k_small_cols, dim3(pl.nchunk), dim3(kBlock), 0, stream, pl.nchunk, (const Chunk*)pl.chunks,
-                         (const int32_t*)upload(wlo), (const uint16_t*)pl.col16, (const int32_t*)pl.col32, pl.s_col);
   }
   // B's slots hold four planes (the two-vector pass of the checks), Ā's two
   pl.slots = alloc<double>((&pl == &plan_b ? 4 : 2) * (size_t)std::max<int64_t>(t.nslot, 1));
@@ -1142,31 +1124,44 @@ void qpg_solver::upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t
   const int64_t layout[8] = {nnz, t.n_c16, t.n_c32, (int64_t)t.tiles.size(), wtiles, staged, t.nslot,
                              (int64_t)t.chunks.size()};
   std::copy(layout, layout + 8, pl.layout);
-  HIPCHK(hipStreamSynchronize(stream));  // t's host arrays go out of scope
-  free_tracked(lstart);
-  free_tracked(llen);
+  HIPCHK(hipStreamSynchronize(stream));  // host arrays go out of scope
+}
+
+// The entries in SELL order (CSR index and column of every position), written on the device from the
+// lanes and the pattern's columns dcol, already there, instead of being built on the host and uploaded.
+void qpg_solver::build_entries(DevPlan& pl, const TilePlan& t, int64_t nnz, const int32_t* dcol) {
+  const DeviceArena::Mark lanes = arena.mark();
+  int32_t* lstart = upload(t.lstart);
+  int32_t* llen = upload(t.llen);
+  const int g = std::max(1, std::min(pl.ntiles, 65536));
+  hipLaunchKernelGGL(k_sell_build, dim3(g), dim3(kBlock), 0, stream, (const Tile*)pl.tiles, pl.ntiles,
+                     (const Chunk*)pl.chunks, (int64_t)t.chunks.size(), (const int32_t*)lstart,
+                     (const int32_t*)llen, dcol, nnz, pl.src, t.n_src, pl.col16, t.n_c16, pl.col32, t.n_c32);
+  std::vector<int32_t> wlo;
+  if (pl.s_col && pl.nchunk) {
+    wlo.resize(t.chunks.size());
+    for (const Tile& x : t.tiles)
+      for (int32_t ci = x.chunk0; ci < x.chunk0 + x.nchunk; ++ci) wlo[ci] = x.wlen > 0 ? x.wlo : -1;
+    hipLaunchKernelGGL(k_small_cols, dim3(pl.nchunk), dim3(kBlock), 0, stream, pl.nchunk, (const Chunk*)pl.chunks,
+                       (const int32_t*)upload(wlo), (const uint16_t*)pl.col16, (const int32_t*)pl.col32, pl.s_col);
+  }
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(stream));
+  arena.rewind(lanes);
 }
 
 // Values in the plan's SELL order (zero in the padding), gathered on the device from the
 // equilibrated CSR values through the plan's CSR index of every SELL position; FP32 copies cast
 // from them.
-void qpg_solver::place_values(DevPlan& pl, const double* csr_val, bool fp32) {
+void qpg_solver::place_values(DevPlan& pl, const double* csr_val) {
   const size_t count = (size_t)pl.nsrc;
-  pl.val64 = alloc<double>(count);
-  if (count) {
-    const int g = (int)std::min<size_t>((count + kBlock - 1) / kBlock, 65536);
-    hipLaunchKernelGGL(k_gather_values, dim3(g), dim3(kBlock), 0, stream, (int64_t)count, (const int32_t*)pl.src,
-                       csr_val, pl.val64);
-  }
-  if (fp32) {
-    pl.val32 = alloc<float>(count);
-    if (count)
-      hipLaunchKernelGGL((k_cast<float, double>), dim3(grid_for((int)count)), dim3(kBlock), 0, stream,
-                         (int)count, pl.val32, (const double*)pl.val64);
-  }
-  HIPCHK(hipStreamSynchronize(stream));
-  free_tracked(pl.src);
-  pl.src = nullptr;
+  if (!count) return;
+  const int g = (int)std::min<size_t>((count + kBlock - 1) / kBlock, 65536);
+  hipLaunchKernelGGL(k_gather_values, dim3(g), dim3(kBlock), 0, stream, (int64_t)count, (const int32_t*)pl.src,
+                     csr_val, pl.val64);
+  if (pl.val32)
+    hipLaunchKernelGGL((k_cast<float, double>), dim3(grid_for((int)count)), dim3(kBlock), 0, stream,
+                       (int)count, pl.val32, (const double*)pl.val64);
 }
 
 // Modified Ruiz equilibration (Algorithm 2) of the uploaded raw problem, on the device (see
@@ -1393,16 +1388,24 @@ int qpg_setup(qpg_solver** out, const qpg_csc* P_triu, const double* q, const qp
     if (plan_err_a) std::rethrow_exception(plan_err_a);
     if (plan_err_b) std::rethrow_exception(plan_err_b);
     mark("work lists (wait for the host thread)", nullptr);
-    h->upload_plan(h->plan_a, ta, H.a_ptr, H.m, h->a_col);
-    h->upload_plan(h->plan_b, tb, H.b_ptr, H.n, h->b_col);
-    mark("work-list uploads", h->stream);
+    h->upload_plan(h->plan_a, ta, h->nnzA, H.m);
+    h->upload_plan(h->plan_b, tb, h->nnzB, H.n);
     if (std::max(h->plan_a.ncomb, h->plan_b.ncomb) > maxgrid) {
       maxgrid = std::max(h->plan_a.ncomb, h->plan_b.ncomb);
       h->rb.partials = h->alloc<double>((size_t)maxgrid * kMaxSlots);
     }
     if (settings->precision == QPG_MIXED) h->alloc_prec32();
-    h->place_values(h->plan_a, h->p64.a_val, settings->precision == QPG_MIXED);
-    h->place_values(h->plan_b, h->p64.b_val, settings->precision == QPG_MIXED);
+    // what follows up to the rewind is needed during setup only
+    const DeviceArena::Mark setup = h->arena.mark();
+    for (DevPlan* pl : {&h->plan_a, &h->plan_b}) pl->src = h->alloc<int32_t>((size_t)pl->nsrc);
+    h->build_entries(h->plan_a, ta, h->nnzA, h->a_col);
+    h->build_entries(h->plan_b, tb, h->nnzB, h->b_col);
+    mark("work-list uploads", h->stream);
+    h->place_values(h->plan_a, h->p64.a_val);
+    h->place_values(h->plan_b, h->p64.b_val);
+    HIPCHK(hipStreamSynchronize(h->stream));
+    h->arena.rewind(setup);
+    for (DevPlan* pl : {&h->plan_a, &h->plan_b}) pl->src = nullptr;
     h->plan_small<double>();
     if (settings->precision == QPG_MIXED) h->plan_small<float>();
     mark("values into SELL order", h->stream);

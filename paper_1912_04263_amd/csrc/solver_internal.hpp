@@ -79,18 +79,41 @@ struct Prec {
 // 16, then 64 MB; larger ones, and any when the device has no room for a block, are allocations of their
 // own. An allocation of 4 MB or more costs 15–500 µs and its release up to 240 µs (releases beyond what
 // the runtime keeps wait for the device): a learned-preconditioner instance of 2·10⁶ entries made about 90, 9
-// of its 25 ms in the release alone (now 2, and 14 in all).
+// of its 25 ms in the release alone (now 2, and 14 in all). What a stage needs only for itself is taken after
+// mark() and given back by rewind(): blocks that came since to the device, the rest to the next requests.
 struct DeviceArena {
   static constexpr size_t kCarve = size_t(16) << 20, kAlign = 256;
-  std::vector<void*> blocks, own;
+  struct Block {
+    void* p;
+    size_t bytes;
+  };
+  std::vector<Block> blocks, own;
   size_t next = size_t(1) << 20, left = 0;
   char* at = nullptr;
+  size_t held = 0, used = 0;  // bytes of all allocations, and handed out of them
   DeviceArena() = default;
   DeviceArena(const DeviceArena&) = delete;
   DeviceArena& operator=(const DeviceArena&) = delete;
-  ~DeviceArena() {
-    for (void* p : own) (void)hipFree(p);
-    for (void* p : blocks) (void)hipFree(p);
+  ~DeviceArena() { rewind(Mark{}); }
+  struct Mark {
+    size_t blocks = 0, own = 0, next = 0, left = 0, used = 0;
+    char* at = nullptr;
+  };
+  Mark mark() const { return Mark{blocks.size(), own.size(), next, left, used, at}; }
+  // the device must be done with what is given back
+  void rewind(const Mark& m) {
+    auto drop = [this](std::vector<Block>& v, size_t keep) {
+      for (; v.size() > keep; v.pop_back()) {
+        (void)hipFree(v.back().p);
+        held -= v.back().bytes;
+      }
+    };
+    drop(own, m.own);
+    drop(blocks, m.blocks);
+    next = m.next;
+    left = m.left;
+    used = m.used;
+    at = m.at;
   }
   void* get(size_t bytes, const char* what) {
     bytes = (std::max<size_t>(bytes, 1) + kAlign - 1) / kAlign * kAlign;
@@ -99,7 +122,8 @@ struct DeviceArena {
       blocks.reserve(blocks.size() + 1);
       void* p = nullptr;
       if (hipMalloc(&p, next) == hipSuccess) {
-        blocks.push_back(p);
+        blocks.push_back({p, next});
+        held += next;
         at = static_cast<char*>(p);
         left = next;
         next = std::min(4 * next, size_t(64) << 20);
@@ -111,20 +135,21 @@ struct DeviceArena {
       void* p = at;
       at += bytes;
       left -= bytes;
+      used += bytes;
       return p;
     }
     own.reserve(own.size() + 1);
     void* p = nullptr;
     const hipError_t e = hipMalloc(&p, bytes);
     if (e != hipSuccess) throw HipError{e, what};
-    own.push_back(p);
+    adopt(p, bytes);
     return p;
   }
-  void release(void* p) {
-    auto it = std::find(own.begin(), own.end(), p);
-    if (it == own.end()) return;
-    own.erase(it);
-    HIPCHK(hipFree(p));
+  // an allocation made elsewhere
+  void adopt(void* p, size_t bytes) {
+    own.push_back({p, bytes});
+    held += bytes;
+    used += bytes;
   }
 };
 
@@ -155,7 +180,7 @@ struct DevPlan {
   uint16_t *s_segslot = nullptr, *s_rowslot = nullptr, *s_col = nullptr;
   bool s_rows = false;  // segments_are_rows
   int32_t nchunk = 0;
-  int32_t* src = nullptr;  // CSR index of every SELL position, on the device until the values are placed
+  int32_t* src = nullptr;  // CSR index of every SELL position, during setup until the values are placed
   int64_t nsrc = 0;
 };
 
@@ -224,8 +249,6 @@ struct qpg_solver {
   T* alloc(size_t count) {
     return static_cast<T*>(arena.get(std::max<size_t>(count, 1) * sizeof(T), "hipMalloc"));
   }
-  // frees a large block from alloc before the solver ends (small ones go with it)
-  void free_tracked(void* ptr) { arena.release(ptr); }
   template <typename T, class A>
   T* upload(const std::vector<T, A>& h) {
     T* d = alloc<T>(h.size());
@@ -503,9 +526,9 @@ struct qpg_solver {
   int solve();
   TilePlan plan_tiles(const std::vector<int32_t>& rowptr, const int32_t* col, int32_t nrows,
                       int32_t ncols) const;
-  void upload_plan(DevPlan& pl, TilePlan& t, const std::vector<int32_t>& rowptr, int32_t nrows,
-                   const int32_t* dcol);
-  void place_values(DevPlan& pl, const double* csr_val, bool fp32);
+  void upload_plan(DevPlan& pl, TilePlan& t, int64_t nnz, int32_t nrows);
+  void build_entries(DevPlan& pl, const TilePlan& t, int64_t nnz, const int32_t* dcol);
+  void place_values(DevPlan& pl, const double* csr_val);
   void alloc_prec64(const HostProblem& H);
   void place_raw(const HostProblem& H);
   void alloc_prec32();

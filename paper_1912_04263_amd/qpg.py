@@ -92,6 +92,7 @@ SIGNATURES = {
     "qpg_time_kernel": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, _PD]),
     "qpg_spmv_layout": (C.c_int, [C.c_void_p, C.c_int32, C.POINTER(C.c_int64)]),
     "qpg_small_level": (C.c_int, [C.c_void_p, C.c_int32, _PI]),
+    "qpg_device_bytes": (C.c_int, [C.c_void_p, C.POINTER(C.c_int64)]),
     "qpg_cleanup": (C.c_int, [C.c_void_p]),
     "qpg_get_kdiag": (C.c_int, [C.c_void_p, C.c_double, _PD]),
     "qpg_hutchinson": (C.c_int, [C.c_void_p, _PB, C.c_int32, C.c_double, C.c_double, C.c_int32, _PD]),
@@ -309,6 +310,12 @@ class Solver:
         level = C.c_int32()
         self._check(lib().qpg_small_level(self._h, precision, C.byref(level)))
         return level.value
+
+    def device_bytes(self):
+        """Device memory of the handle: (bytes allocated, bytes of them in use)."""
+        out = (C.c_int64 * 2)()
+        self._check(lib().qpg_device_bytes(self._h, out))
+        return int(out[0]), int(out[1])
 
     def kdiag(self, rho: float):
         out = np.empty(self.n)
