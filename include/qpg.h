@@ -276,6 +276,9 @@ int qpg_get_kdiag(const qpg_solver* h, double rho, double* kdiag);
  * probes z_k given in `signs` (s×n, row-major, entries ±1 only; the caller draws them), each
  * K⁻¹z_k by the solver's own Jacobi PCG (Algorithm 3) from 0 to ‖r‖∞ ≤ eps‖z‖∞ or max_iter.
  * Writes n values to diag. Not part of the paper: training targets of QPG_PRECOND_LEARNED.
+ * The first call on a handle allocates its network's graph data, which stay. Several probes are solved four at a
+ * time, in vectors of 32·(4n + m + segments of the work lists) bytes: up to 64 MB of them stay with the handle as
+ * well, larger ones are freed before the call returns. Without room for them the probes are solved one by one.
  * QPG_ERR_STATE for a handle set up with settings.rho_vector (K is taken with R = ρ̄I here). */
 int qpg_hutchinson(qpg_solver* h, const int8_t* signs, int32_t nprobes, double rho, double eps,
                    int32_t max_iter, double* diag);

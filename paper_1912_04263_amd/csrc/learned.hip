@@ -56,7 +56,10 @@ struct LearnedState {
   NetScalars* ns_host = nullptr;
   double* acc = nullptr;    // Hutchinson accumulator (n)
   int8_t* probe = nullptr;  // one probe (n), or kMulti of them
-  // kMulti solves at once (multi.hpp), allocated on their first use
+  // kMulti solves at once (multi.hpp): vectors of up to kMultiKeep bytes stay from their first use on, larger
+  // ones go at the end of the call that made them
+  static constexpr size_t kMultiKeep = size_t(64) << 20;
+  void* mlarge = nullptr;
   MultiVec *mx = nullptr, *mr = nullptr, *mp = nullptr, *mkp = nullptr, *mslots = nullptr;
   MultiState* mst = nullptr;
   MultiRead* mread = nullptr;  // mapped host memory
@@ -70,6 +73,13 @@ struct LearnedState {
   T* alloc(size_t count) {
     return static_cast<T*>(arena.get(count * sizeof(T), "hipMalloc (learned preconditioner)"));
   }
+  void end_multi() {
+    if (!mlarge) return;
+    (void)hipFree(mlarge);
+    mlarge = nullptr;
+    mst = nullptr;
+  }
+  ~LearnedState() { end_multi(); }
 };
 
 void destroy_learned(LearnedState* L) {
@@ -456,8 +466,8 @@ int hutchinson_run(qpg_solver* h, const int8_t* signs, int32_t nprobes, double r
   return QPG_OK;
 }
 
-// The vectors of kMulti solves, on first use. False when the device has no room for them: the probes are
-// then solved one by one.
+// The vectors of kMulti solves, where they are not there. False when the device has no room for them: the probes
+// are then solved one by one.
 bool ensure_multi(qpg_solver* h, LearnedState* L) {
   if (L->mst) return true;
   const size_t n = h->n, m = h->m;
@@ -475,7 +485,10 @@ bool ensure_multi(qpg_solver* h, LearnedState* L) {
     return false;
   }
   HIPCHK(e);
-  L->arena.adopt(p, bytes);
+  if (bytes <= LearnedState::kMultiKeep)
+    L->arena.adopt(p, bytes);
+  else
+    L->mlarge = p;
   L->mx = (MultiVec*)p;
   L->mr = L->mx + n;
   L->mkp = L->mr + n;
@@ -629,8 +642,13 @@ int qpg_hutchinson(qpg_solver* h, const int8_t* signs, int32_t nprobes, double r
     HIPCHK(hipSetDevice(h->device));
     LearnedState* L = ensure_graph(h);
     // several probes at once, except one alone and the problems of the one-workgroup kernels
-    if (nprobes > 1 && !h->use_small<double>() && ensure_multi(h, L))
+    if (nprobes > 1 && !h->use_small<double>() && ensure_multi(h, L)) {
+      struct End {
+        LearnedState* L;
+        ~End() { L->end_multi(); }
+      } end{L};
       return hutchinson_multi(h, L, signs, nprobes, rho, eps, max_iter, diag);
+    }
     return hutchinson_run(h, signs, nprobes, rho, eps, max_iter, diag, L->acc, L->probe);
   } catch (const HipError& e) {
     return hutchinson_device_error(h, e);
