@@ -430,42 +430,6 @@ int hutchinson_check(qpg_solver* h, const int8_t* signs, int32_t nprobes, double
   return QPG_OK;
 }
 
-// (1/s) Σ_k z_k ∘ K⁻¹z_k with K⁻¹z_k by the solver's Jacobi PCG from 0; acc (n doubles) and probe
-// (n bytes) are device buffers the caller provides. ρ̄ and the Jacobi diagonal are restored.
-int hutchinson_run(qpg_solver* h, const int8_t* signs, int32_t nprobes, double rho, double eps,
-                   int32_t max_iter, double* diag, double* acc, int8_t* probe) {
-  Prec<double>& V = h->p64;
-  const int n = h->n;
-  const double rho_saved = h->rho_cur;
-  struct Restore {  // ρ̄ of the handle is restored on every way out
-    qpg_solver* h;
-    double rho;
-    ~Restore() { h->rho_cur = rho; }
-  } restore{h, rho_saved};
-  h->rho_cur = rho;
-  h->jacobi<double>(rho);
-  h->fill(acc, n, 0.0);
-  for (int k = 0; k < nprobes; ++k) {
-    HIPCHK(hipMemcpyAsync(probe, signs + (size_t)k * n, n, hipMemcpyHostToDevice, h->stream));
-    hipLaunchKernelGGL((k_probe_load<double>), dim3(h->vgrid), dim3(kBlock), 0, h->stream, n,
-                       (const int8_t*)probe, V.b);
-    h->fill(V.xt, n, 0.0);
-    hipLaunchKernelGGL((k_absmax<double>), dim3(h->vgrid), dim3(kBlock), 0, h->stream, n,
-                       (const double*)V.b, h->rb.partials);
-    h->finalize_fn<1, 1u>(FinThresh{h->st, eps, 1}, h->vgrid);
-    h->last_pcg = 1;
-    h->pcg_solve<double>(rho, max_iter);
-    hipLaunchKernelGGL((k_probe_acc<double>), dim3(h->vgrid), dim3(kBlock), 0, h->stream, n,
-                       (const int8_t*)probe, (const double*)V.xt, acc);
-  }
-  HIPCHK(hipMemcpyAsync(diag, acc, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(hipStreamSynchronize(h->stream));
-  for (int i = 0; i < n; ++i) diag[i] /= nprobes;
-  h->jacobi<double>(rho_saved);
-  HIPCHK(hipGetLastError());
-  return QPG_OK;
-}
-
 // The vectors of kMulti solves, where they are not there. False when the device has no room for them: the probes
 // are then solved one by one.
 bool ensure_multi(qpg_solver* h, LearnedState* L) {
@@ -526,10 +490,69 @@ int multi_pass(qpg_solver* h, LearnedState* L, const DevPlan& pl, int nsplit, in
   return pl.ncomb;
 }
 
-// hutchinson_run with kMulti probes at a time: bitwise the same estimate. Measured on the 20,000-asset
-// portfolio (16 probes, about 162 PCG steps each): 97 ms one by one, 33 ms four at a time.
-int hutchinson_multi(qpg_solver* h, LearnedState* L, const int8_t* signs, int32_t nprobes, double rho, double eps,
-                     int32_t max_iter, double* diag) {
+// `count` ≤ kMulti probes of hutchinson_run in one solve: bitwise the same numbers. `predicted`: PCG steps that the
+// last such solve of the call took. Measured on the 20,000-asset portfolio (16 probes, about 162 PCG steps each): 97 ms
+// one by one, 33 ms four at a time.
+void solve_together(qpg_solver* h, LearnedState* L, const int8_t* signs, int count, double rho, double eps,
+                    int32_t max_iter, double* acc, int& predicted) {
+  Prec<double>& V = h->p64;
+  const int n = h->n;
+  MultiVec* w = L->mp + n;
+  const dim3 vg(h->vgrid), vb(kBlock);
+  HIPCHK(hipMemcpyAsync(L->probe, signs, (size_t)count * n, hipMemcpyHostToDevice, h->stream));
+  hipLaunchKernelGGL(k_multi_start, vg, vb, 0, h->stream, n, count, L->mx, L->mp, L->probe, L->mst, eps);
+  multi_pass(h, L, h->plan_a, INT32_MAX, 1, L->mx, MultiScaled{w, rho});
+  const MultiR0 r0{L->mx, L->probe, V.dinv, L->mr, L->mp, h->s.sigma, n, L->mst, max_iter};
+  h->finalize(r0, multi_pass(h, L, h->plan_b, n, 2, L->mp, r0));
+  // iterations between host reads: first as many as the call's last four solves took, then 2, 4, 8, 8, …
+  int issued = 0, batch = predicted, more = 1;
+  for (;;) {
+    const int b = std::min(batch, max_iter - issued);
+    for (int i = 0; i < b; ++i) {
+      const int it = issued + i;
+      multi_pass(h, L, h->plan_a, INT32_MAX, 1, L->mp, MultiScaled{w, rho});
+      const int nkp = multi_pass(h, L, h->plan_b, n, 2, L->mp, MultiKp{L->mp, L->mkp, h->s.sigma});
+      hipLaunchKernelGGL(k_multi_update, vg, vb, 0, h->stream, n, L->mx, L->mr, (const MultiVec*)L->mp,
+                         (const MultiVec*)L->mkp, (const double*)V.dinv, L->mst, (const double*)h->rb.partials, nkp,
+                         h->rb.vpartials, it);
+      hipLaunchKernelGGL(k_multi_dir, vg, vb, 0, h->stream, n, L->mp, (const MultiVec*)L->mr,
+                         (const double*)V.dinv, L->mst, (const double*)h->rb.vpartials, h->vgrid, it);
+    }
+    issued += b;
+    hipLaunchKernelGGL(k_multi_read, dim3(1), dim3(64), 0, h->stream, (const MultiState*)L->mst, L->mread_dev,
+                       ++L->mreads);
+    h->spin(&L->mread->seq, L->mreads);
+    if (L->mread->all_done || issued >= max_iter) break;
+    batch = more = std::min(2 * more, 8);
+  }
+  predicted = std::max(1, L->mread->iter);
+  hipLaunchKernelGGL(k_multi_acc, vg, vb, 0, h->stream, n, count, (const int8_t*)L->probe, (const MultiVec*)L->mx,
+                     acc);
+}
+
+// The fewest probes that are worth solving together. Four solves at a time cost this many times one alone: 1.4–2.0
+// where its latencies bound it (up to 80 MB of matrices in windows of at most 2048 columns, 128 MB without windows),
+// 2.2–2.9 beyond, and 2.6–4.9 where a window of 32 bytes per column does not fit in LDS, so that every gather
+// goes to the caches: there it pays for four, with matrices (256 MB) and vectors (10 MB) in them. 40 steps of
+// two / three / four probes, one by one → together: SVM with 2·10⁶ entries 3.0 / 4.5 / 5.9 → 2.5 / 2.6 / 2.6 ms,
+// random with 2·10⁷ and no windows 23.4 / 35.0 / 46.7 → 28.4 / 28.6 / 28.9, Lasso with 10⁷ 6.2 / 9.1 / 12.1
+// → 10.7 / 11.1 / 11.4, SVM with 10⁸ 44 / 66 / 88 → 105 / 108 / 111.
+int together_from(const qpg_solver* h) {
+  if (h->use_small<double>()) return INT32_MAX;
+  const int64_t mats = ((int64_t)h->nnzA + h->nnzB) * (int64_t)(sizeof(double) + sizeof(uint16_t));
+  const int64_t vecs = ((int64_t)h->n + h->m) * (int64_t)sizeof(MultiVec);
+  const int wlen = std::max(h->plan_a.max_wlen, h->plan_b.max_wlen);
+  if ((int64_t)wlen * (int64_t)sizeof(MultiVec) > h->lds_max)
+    return mats <= qpg_solver::kStreamAll && vecs <= 10000000 ? kMulti : INT32_MAX;
+  return vecs <= 20000000 && wlen <= 2048 && mats <= (wlen ? 80000000 : 128000000) ? 2 : 3;
+}
+
+// (1/s) Σ_k z_k ∘ K⁻¹z_k with K⁻¹z_k by the solver's Jacobi PCG from 0; acc (n doubles) and probe
+// (n bytes) are device buffers the caller provides. ρ̄ and the Jacobi diagonal are restored. With L, groups of at
+// least `from` probes are solved together.
+int hutchinson_run(qpg_solver* h, const int8_t* signs, int32_t nprobes, double rho, double eps,
+                   int32_t max_iter, double* diag, double* acc, int8_t* probe, LearnedState* L = nullptr,
+                   int from = INT32_MAX) {
   Prec<double>& V = h->p64;
   const int n = h->n;
   const double rho_saved = h->rho_cur;
@@ -540,43 +563,30 @@ int hutchinson_multi(qpg_solver* h, LearnedState* L, const int8_t* signs, int32_
   } restore{h, rho_saved};
   h->rho_cur = rho;
   h->jacobi<double>(rho);
-  h->fill(L->acc, n, 0.0);
-  MultiVec* w = L->mp + n;
-  const dim3 vg(h->vgrid), vb(kBlock);
+  h->fill(acc, n, 0.0);
   int predicted = 1;  // nothing is carried over from an earlier call
-  for (int k = 0; k < nprobes; k += kMulti) {
+  for (int k = 0; k < nprobes;) {
+    const int8_t* z = signs + (size_t)k * n;
     const int count = std::min<int>(kMulti, nprobes - k);
-    HIPCHK(hipMemcpyAsync(L->probe, signs + (size_t)k * n, (size_t)count * n, hipMemcpyHostToDevice, h->stream));
-    hipLaunchKernelGGL(k_multi_start, vg, vb, 0, h->stream, n, count, L->mx, L->mp, L->probe, L->mst, eps);
-    multi_pass(h, L, h->plan_a, INT32_MAX, 1, L->mx, MultiScaled{w, rho});
-    const MultiR0 r0{L->mx, L->probe, V.dinv, L->mr, L->mp, h->s.sigma, n, L->mst, max_iter};
-    h->finalize(r0, multi_pass(h, L, h->plan_b, n, 2, L->mp, r0));
-    // iterations between host reads: first as many as the call's last four solves took, then 2, 4, 8, 8, …
-    int issued = 0, batch = predicted, more = 1;
-    for (;;) {
-      const int b = std::min(batch, max_iter - issued);
-      for (int i = 0; i < b; ++i) {
-        const int it = issued + i;
-        multi_pass(h, L, h->plan_a, INT32_MAX, 1, L->mp, MultiScaled{w, rho});
-        const int nkp = multi_pass(h, L, h->plan_b, n, 2, L->mp, MultiKp{L->mp, L->mkp, h->s.sigma});
-        hipLaunchKernelGGL(k_multi_update, vg, vb, 0, h->stream, n, L->mx, L->mr, (const MultiVec*)L->mp,
-                           (const MultiVec*)L->mkp, (const double*)V.dinv, L->mst, (const double*)h->rb.partials, nkp,
-                           h->rb.vpartials, it);
-        hipLaunchKernelGGL(k_multi_dir, vg, vb, 0, h->stream, n, L->mp, (const MultiVec*)L->mr,
-                           (const double*)V.dinv, L->mst, (const double*)h->rb.vpartials, h->vgrid, it);
-      }
-      issued += b;
-      hipLaunchKernelGGL(k_multi_read, dim3(1), dim3(64), 0, h->stream, (const MultiState*)L->mst, L->mread_dev,
-                         ++L->mreads);
-      h->spin(&L->mread->seq, L->mreads);
-      if (L->mread->all_done || issued >= max_iter) break;
-      batch = more = std::min(2 * more, 8);
+    if (L && count >= from) {
+      solve_together(h, L, z, count, rho, eps, max_iter, acc, predicted);
+      k += count;
+      continue;
     }
-    predicted = std::max(1, L->mread->iter);
-    hipLaunchKernelGGL(k_multi_acc, vg, vb, 0, h->stream, n, count, (const int8_t*)L->probe, (const MultiVec*)L->mx,
-                       L->acc);
+    HIPCHK(hipMemcpyAsync(probe, z, n, hipMemcpyHostToDevice, h->stream));
+    hipLaunchKernelGGL((k_probe_load<double>), dim3(h->vgrid), dim3(kBlock), 0, h->stream, n,
+                       (const int8_t*)probe, V.b);
+    h->fill(V.xt, n, 0.0);
+    hipLaunchKernelGGL((k_absmax<double>), dim3(h->vgrid), dim3(kBlock), 0, h->stream, n,
+                       (const double*)V.b, h->rb.partials);
+    h->finalize_fn<1, 1u>(FinThresh{h->st, eps, 1}, h->vgrid);
+    h->last_pcg = 1;
+    h->pcg_solve<double>(rho, max_iter);
+    hipLaunchKernelGGL((k_probe_acc<double>), dim3(h->vgrid), dim3(kBlock), 0, h->stream, n,
+                       (const int8_t*)probe, (const double*)V.xt, acc);
+    ++k;
   }
-  HIPCHK(hipMemcpyAsync(diag, L->acc, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+  HIPCHK(hipMemcpyAsync(diag, acc, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
   for (int i = 0; i < n; ++i) diag[i] /= nprobes;
   h->jacobi<double>(rho_saved);
@@ -641,13 +651,13 @@ int qpg_hutchinson(qpg_solver* h, const int8_t* signs, int32_t nprobes, double r
   try {
     HIPCHK(hipSetDevice(h->device));
     LearnedState* L = ensure_graph(h);
-    // several probes at once, except one alone and the problems of the one-workgroup kernels
-    if (nprobes > 1 && !h->use_small<double>() && ensure_multi(h, L)) {
+    const int from = together_from(h);
+    if (nprobes >= from && ensure_multi(h, L)) {
       struct End {
         LearnedState* L;
         ~End() { L->end_multi(); }
       } end{L};
-      return hutchinson_multi(h, L, signs, nprobes, rho, eps, max_iter, diag);
+      return hutchinson_run(h, signs, nprobes, rho, eps, max_iter, diag, L->acc, L->probe, L, from);
     }
     return hutchinson_run(h, signs, nprobes, rho, eps, max_iter, diag, L->acc, L->probe);
   } catch (const HipError& e) {

@@ -1,0 +1,64 @@
+"""Which probes of a Hutchinson estimate are solved together, and what that costs. Needs an MI355X.
+
+Windows of 32 bytes per column that fit in LDS up to 2048 and up to 4096 columns, ones that don't, with vectors in
+the caches and beyond, and no windows: groups of two, of three, of four, and none are solved together. Estimates
+are bitwise those of probes solved one by one, whole groups and remainders.
+"""
+import statistics
+import sys
+import time
+
+import numpy as np
+import pytest
+
+from paper_1912_04263_amd import problems as pr
+from paper_1912_04263_amd import qpg
+
+pytestmark = pytest.mark.gpu
+
+PROBLEMS = {
+    "windows of 2048": lambda: pr.lasso_qp(1_000, 20_000, 0.05, 3),
+    "windows of 4096": lambda: pr.lasso_qp(2_000, 40_000, 0.06, 3),
+    "wide windows": lambda: pr.portfolio_qp(50_000, 500, 0.5, 3),
+    "wide windows, long vectors": lambda: pr.svm_qp(400_000, 100, 0.2, 3),
+    "no windows": lambda: pr.random_qp(30_000, 30_000, 1e-4, 4e-3, 3),
+    "no windows, long vectors": lambda: pr.random_qp(50_000, 700_000, 2e-5, 1e-4, 3),
+}
+
+
+def probes(k, n):
+    return np.random.default_rng(k).choice(np.array([-1, 1], dtype=np.int8), size=(k, n))
+
+
+@pytest.mark.parametrize("name", sorted(PROBLEMS))
+def test_groups_equal_probes_one_by_one(name):
+    p = PROBLEMS[name]()
+    with qpg.Solver.from_qp(p) as s:
+        for k in (1, 2, 3, 4, 5, 6, 7):
+            print("[case] hutchinson groups", name, k, file=sys.stderr, flush=True)
+            z = probes(k, p.n)
+            got = s.hutchinson(z, 0.3, eps=1e-6, max_iter=25)
+            assert np.array_equal(got, s.hutchinson_noalloc(z, 0.3, eps=1e-6, max_iter=25)), k
+
+
+@pytest.mark.parametrize("name", sorted(PROBLEMS))
+@pytest.mark.parametrize("k", [2, 3, 4, 5])
+def test_together_is_not_slower(name, k):
+    """40 PCG steps for each probe. Four solves at once cost up to 4.5 times one where their windows don't fit in LDS:
+    two probes on the longest vectors took 2.0 times as long together. 1.4 is far from that and from noise."""
+    p = PROBLEMS[name]()
+    z = probes(k, p.n)
+
+    def best(f):
+        t = []
+        for _ in range(6):
+            a = time.perf_counter()
+            f(z, 0.3, eps=1e-300, max_iter=40)
+            t.append(time.perf_counter() - a)
+        return statistics.median(t[1:])
+
+    with qpg.Solver.from_qp(p) as s:
+        print("[case] hutchinson time", name, k, file=sys.stderr, flush=True)
+        one, got = best(s.hutchinson_noalloc), best(s.hutchinson)
+    print("[case] one by one %.2f ms, as called %.2f ms" % (1e3 * one, 1e3 * got), file=sys.stderr, flush=True)
+    assert got <= 1.4 * one
