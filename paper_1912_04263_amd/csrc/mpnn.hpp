@@ -121,7 +121,8 @@ __global__ __launch_bounds__(kBlock) void k_spmm32(const Piece* __restrict__ pac
 // LDS, the next one's loads in flight meanwhile; CH·F lanes then add it, lane (g, f) the entries ≡ g mod
 // CH of feature f in order. On the portfolio graph (rows of 10⁴ and 2·10⁴ entries) one workgroup per row that
 // gathered as it added took 282 µs on average (525 at most); now 49 µs with 16 features per workgroup, bound
-// by the batches of the longest row that follow one another (8 features: 60 µs, for 4 times the requests). Splitting such rows into pieces took 24 µs, but adds in another order.
+// by the batches of the longest row that follow one another (8 features: 60 µs, for 4 times the requests).
+// Splitting such rows into pieces took 24 µs, but adds in another order.
 constexpr int kSpmmBlock = 512;
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 template <int CH, int F>

@@ -1,5 +1,5 @@
 // Small problems: ADMM iterations up to and including the next residual check that needs the host, or a
-// whole PCG solve, in one launch of one workgroup. Included by solver.hip only.
+// whole PCG solve, in one launch of one workgroup.
 //
 // A problem of some hundred variables keeps the general path (one kernel per pass, 6 per PCG step
 // and 5 more per ADMM iteration) at 2–3 µs per kernel on the device and 3.5–6 µs per launch on the

@@ -2,7 +2,7 @@
 
 A wavefront takes a pack of at most 16 rows of at most 16 entries or of 8 rows of at most 256; longer rows
 have workgroups of their own, which add them in one chain up to 2048 entries and in 8 chains above, in
-batches of 256 and 1024 entries; edge weights go by pieces of 512. The rows of Ā (and, transposed, of Āᵀ)
+batches of 256 and 512 entries; edge weights go by pieces of 512. The rows of Ā (and, transposed, of Āᵀ)
 have lengths on both sides of each of these limits. Float32 layers, against the float64 oracle; tolerance as
 for the other float32 comparisons of the network (1e-4 of the largest value): the weights of a row sum
 to 1, so a sum of up to 9000 float32 products is within 9000·2⁻²⁴ ≈ 5.4e-4 of its largest term in the

@@ -1,8 +1,8 @@
 """qpg_hutchinson_noalloc (the allocation-free Hutchinson estimate) against qpg_hutchinson. Needs an
 MI355X.
 
-Both calls run the same kernels in the same order on the same probes, so the estimates must agree
-bitwise. The no-alloc call keeps its accumulator and probe in one static device array shared by
+Both calls add the same numbers in the same order, one of them for up to four probes at a time, so the
+estimates must agree bitwise. The no-alloc call keeps its accumulator and probe in one static device array shared by
 every call on the device: two calls in a row, the second on a smaller problem with fewer probes,
 check that nothing of the first call leaks into the second. The small problem is also checked
 against the oracle's diag(K⁻¹) estimate with a dense inverse (1e-8, as for qpg_hutchinson).
