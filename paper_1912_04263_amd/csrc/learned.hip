@@ -469,17 +469,8 @@ int multi_pass(qpg_solver* h, LearnedState* L, const DevPlan& pl, int nsplit, in
   const size_t want = (size_t)pl.max_wlen * sizeof(MultiVec);
   const int staged = want <= (size_t)h->lds_max;
   const size_t lds = staged ? want : 0;
-  static std::atomic<size_t> allowed[64];
-  const bool tab = h->device >= 0 && h->device < 64;
-  if (!tab || lds > allowed[h->device].load(std::memory_order_relaxed)) {
-    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_multi_spmv),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    if (tab) {
-      size_t cur = allowed[h->device].load(std::memory_order_relaxed);
-      while (cur < lds && !allowed[h->device].compare_exchange_weak(cur, lds)) {
-      }
-    }
-  }
+  static LdsLimit limit;
+  allow_lds(limit, reinterpret_cast<const void*>(&k_multi_spmv), lds, h->device);
   hipLaunchKernelGGL(k_multi_spmv, dim3(pl.ntiles), dim3(kMultiBlock), lds, h->stream, (const Tile*)pl.tiles,
                      (const Chunk*)pl.chunks, (const int32_t*)pl.segslot, (const uint16_t*)pl.col16,
                      (const int32_t*)pl.col32, (const double*)pl.val64, nsplit, x, L->mslots, pl.nslot, planes, staged,

@@ -3,9 +3,12 @@
 
 #include <sys/mman.h>
 
+#include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <functional>
+#include <mutex>
 #include <new>
 #include <memory>
 #include <string>
@@ -57,6 +60,27 @@ struct NoInit : std::allocator<T> {
 };
 template <class T>
 using hvec = std::vector<T, NoInit<T>>;
+
+// The dynamic LDS that a kernel may take, a per-device attribute of it: raised before the first launch that needs
+// more. Under a lock, so that a thread that raises it for less cannot come after one that raised it for more.
+class LdsLimit {
+ public:
+  template <class Set>
+  void raise(int device, size_t bytes, Set set) {
+    const bool known = device >= 0 && device < kDevices;
+    if (known && bytes <= allowed[device].load(std::memory_order_acquire)) return;
+    std::lock_guard<std::mutex> lock(mu);
+    std::atomic<size_t>& a = known ? allowed[device] : others;  // others: set at each launch
+    const size_t most = std::max(bytes, a.load(std::memory_order_relaxed));
+    set(most);
+    a.store(most, std::memory_order_release);
+  }
+
+ private:
+  static constexpr int kDevices = 64;
+  std::mutex mu;
+  std::atomic<size_t> allowed[kDevices] = {}, others{0};
+};
 
 // *slot, built on its first use: it is stored only once complete, and destroyed where building throws.
 template <class T, class Build, class Destroy>

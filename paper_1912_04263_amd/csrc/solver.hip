@@ -311,17 +311,8 @@ namespace {
 // and launch it as one workgroup.
 template <typename T, bool ML, void (*KERNEL)(SmallArgs<T>)>
 void launch_small(const SmallArgs<T>& a, size_t lds, int device, hipStream_t stream) {
-  static std::atomic<size_t> allowed[64];
-  const bool tab = device >= 0 && device < 64;
-  if (!tab || lds > allowed[device].load(std::memory_order_relaxed)) {
-    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds));
-    if (tab) {
-      size_t cur = allowed[device].load(std::memory_order_relaxed);
-      while (cur < lds && !allowed[device].compare_exchange_weak(cur, lds)) {
-      }
-    }
-  }
+  static LdsLimit limit;
+  allow_lds(limit, reinterpret_cast<const void*>(KERNEL), lds, device);
   hipLaunchKernelGGL(KERNEL, dim3(1), dim3(kSmallBlock<ML>), lds, stream, a);
 }
 

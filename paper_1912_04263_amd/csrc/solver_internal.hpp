@@ -192,6 +192,12 @@ struct SmallPlan {
   SmallLds o{};
 };
 
+inline void allow_lds(LdsLimit& limit, const void* kernel, size_t bytes, int device) {
+  limit.raise(device, bytes, [&](size_t most) {
+    HIPCHK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
+  });
+}
+
 struct LearnedState;  // learned-preconditioner data of a solver (learned.hip)
 void destroy_learned(LearnedState* L);
 hipError_t resolve_noalloc_scratch(int device);  // learned.hip: scratch of qpg_hutchinson_noalloc
@@ -296,20 +302,8 @@ struct qpg_solver {
   template <typename T, class Op, bool STREAM>
   void spmv_stream(const DevPlan& pl, int nsplit, int planes, const Op& op, const int32_t* gate, T* sl, int keep) {
     const size_t shmem = (size_t)pl.max_wlen * sizeof(T);
-    // The dynamic LDS limit is a per-device attribute of each instantiation: raise it once per
-    // device (always, for device ordinals beyond the table).
-    constexpr int kDevTable = 64;
-    static std::atomic<size_t> lds_allowed[kDevTable];
-    const bool tab = device >= 0 && device < kDevTable;
-    if (!tab || shmem > lds_allowed[device].load(std::memory_order_relaxed)) {
-      HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_spmv<T, Op, STREAM>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem));
-      if (tab) {
-        size_t cur = lds_allowed[device].load(std::memory_order_relaxed);
-        while (cur < shmem && !lds_allowed[device].compare_exchange_weak(cur, shmem)) {
-        }
-      }
-    }
+    static LdsLimit limit;
+    allow_lds(limit, reinterpret_cast<const void*>(&k_spmv<T, Op, STREAM>), shmem, device);
     const T* val = std::is_same<T, double>::value ? (const T*)pl.val64 : (const T*)pl.val32;
     hipLaunchKernelGGL((k_spmv<T, Op, STREAM>), dim3(pl.ntiles), dim3(kSpmvBlock), shmem, stream, pl.tiles, pl.chunks,
                        pl.segslot, pl.col16, pl.col32, val, nsplit, keep, op, sl, pl.nslot, planes, gate);
@@ -351,17 +345,8 @@ struct qpg_solver {
     const DevPlan& pl = plan_b;
     T* sl = static_cast<T*>(pl.slots);
     const size_t shmem = (size_t)pl.max_wlen * sizeof(Pair<T>);
-    static std::atomic<size_t> lds_allowed[64];
-    const bool tab = device >= 0 && device < 64;
-    if (!tab || shmem > lds_allowed[device].load(std::memory_order_relaxed)) {
-      HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_spmv2<T, Op>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem));
-      if (tab) {
-        size_t cur = lds_allowed[device].load(std::memory_order_relaxed);
-        while (cur < shmem && !lds_allowed[device].compare_exchange_weak(cur, shmem)) {
-        }
-      }
-    }
+    static LdsLimit limit;
+    allow_lds(limit, reinterpret_cast<const void*>(&k_spmv2<T, Op>), shmem, device);
     const T* val = std::is_same<T, double>::value ? (const T*)pl.val64 : (const T*)pl.val32;
     hipLaunchKernelGGL((k_spmv2<T, Op>), dim3(pl.ntiles), dim3(kSpmvBlock), shmem, stream, pl.tiles, pl.chunks,
                        pl.segslot, pl.col16, pl.col32, val, n, stream_keep<T>(), op, sl, pl.nslot, gate);
